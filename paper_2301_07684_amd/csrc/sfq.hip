@@ -13,12 +13,11 @@
 //                writes every slot of a chunk it updates (whole cache lines), addresses each
 //                chunk from its first element (scalar bases, one 32-bit lane offset), and
 //                carries none of the sampling code, so its register footprint stays small.
-//   emit_kernel  each queue slice is sampled by a few blocks with all lanes busy: Philox draws,
-//                the inverse-CDF tables (L2-resident), recoil and products.  Each block's
-//                product slots come from the queued counts of every earlier slice, which it
-//                sums itself; block 0 adds the step's counters once and the last block out
-//                advances the product counts (per-wave reservations only for beyond-LCFA
-//                photons and per-set products).
+//   emit_kernel  the queued emitters in even shares per wave, all lanes busy: Philox draws, the
+//                inverse-CDF tables (L2-resident), recoil and products.  Every block makes the
+//                prefix sums of the queued counts, which give a lane its entry and its product
+//                slots; block 0 adds the step's counters and advances the product counts
+//                (per-wave reservations only for beyond-LCFA photons and per-set products).
 //   defer_kernel the shares the streaming pass deferred (queue too small), stepped whole.
 //   rates/chi/sample/philox kernels: grid-stride elementwise kernels behind the batched calls.
 #include <hip/hip_runtime.h>
@@ -91,16 +90,13 @@ struct StepArgs {
     // a chunk (STEP_BLOCK/64 waves share a chunk) leaves that share untouched and appends
     // chunk * STEP_WAVES + wave here; the emitter kernel steps those shares afterwards.
     uint32_t* d_list;
-    unsigned* d_ctl;            // [5]: shares deferred, next share to step, deferred-share
-                                // blocks done, emitter blocks done, next chunk to stream
+    unsigned* d_ctl;            // control words, see CTL_*
     unsigned* obs;              // nullable, host-mapped: [0] the largest emitter fraction of a
                                 // wave's share (float bits), [1] shares deferred (for sizing)
-    unsigned* emit_obs;         // nullable, host-mapped: the step's emitters over the particles
-                                // it processed (float bits; picks the emitter pass's grid)
     int grid;                   // blocks of the streaming kernel (STEP_WAVES slices each)
     int max_chunks;             // the most chunks one streaming block takes (the queue's worst
                                 // case is sized for it)
-    int emit_split;             // emitter blocks per streaming block's slices
+    float n_total;              // particle slots of the step
     int may_defer;              // the slices are smaller than the step's worst case (host side:
                                 // the deferred-share kernel is enqueued)
     sfq_products prod[3];       // photons, electrons, positrons
@@ -113,6 +109,12 @@ struct StepArgs {
     int zero_counts;             // the step's product counts start from zero (nsets == 0: the
                                  // emitter kernel takes the bases as 0 instead of reading them)
 };
+
+// The control words (the first 256 bytes of the queue memory, cleared once and left cleared by
+// every step): shares deferred, next deferred share to step, deferred-share blocks done, next
+// chunk to stream; and, written by every step's streaming kernel, the product counts before the
+// step (three 64-bit words), from which the emitter blocks count their slots.
+enum { CTL_DEFERRED = 0, CTL_DEFER_NEXT = 1, CTL_DEFER_DONE = 2, CTL_CHUNK = 4, CTL_BASE = 8 };
 
 enum { CNT_PROCESSED, CNT_EMITTED, CNT_CONVERTED, CNT_REJECTED, CNT_OOD, CNT_CLAMPED, CNT_OVERFLOW,
        CNT_DEFERRED, CNT_N };
@@ -284,26 +286,30 @@ __device__ __forceinline__ unsigned long long wave_reserve(unsigned long long* c
 }
 
 // Slots in per-owner product buffers: the lanes of a wave that want a slot are grouped by their
-// set index (usually one or two distinct sets per wave) and each group takes its slots with one
-// atomic.  Every lane of the wave must call this (the loop is wave-uniform).
+// set index and the first lane of each group takes the group's slots.  The groups' atomics are
+// issued together (one memory round trip however many sets the wave's lanes belong to; one after
+// the other, they made the emitter pass of a six-simulation batch of 3 million particles 65 us
+// instead of 58 at 2 x 2048, and 90 instead of 66 at 4 x 512).
+// Every lane of the wave must call this (the loop is wave-uniform).
 __device__ __forceinline__ unsigned long long keyed_reserve(const sfq_product_set* sets,
                                                             int species, int key, bool want)
 {
     unsigned long long pending = __ballot(want);
+    if (pending == 0) return 0;
     const int lane = lane_id();
-    unsigned long long slot = 0;
+    unsigned long long group = 0;
     while (pending) {
-        const int leader = __ffsll((long long)pending) - 1;
-        const int lk = __shfl(key, leader);
+        const int lk = __builtin_amdgcn_readlane(key, __ffsll((long long)pending) - 1);
         const unsigned long long m = __ballot(want && key == lk);
-        unsigned long long base = 0;
-        if (lane == leader)
-            base = atomicAdd(&sets[lk].product_counts[species], (unsigned long long)__popcll(m));
-        base = __shfl(base, leader);
-        if ((m >> lane) & 1ull) slot = base + (unsigned long long)__popcll(m & ((1ull << lane) - 1ull));
+        if ((m >> lane) & 1ull) group = m;
         pending &= ~m;
     }
-    return slot;
+    const int leader = want ? __ffsll((long long)group) - 1 : lane;
+    unsigned long long base = 0;
+    if (want && lane == leader)
+        base = atomicAdd(&sets[key].product_counts[species], (unsigned long long)__popcll(group));
+    base = __shfl(base, leader);
+    return base + (unsigned long long)__popcll(group & ((1ull << lane) - 1ull));
 }
 
 // =============================================================================================
@@ -331,10 +337,8 @@ constexpr int bulk_waves(bool mixed, bool blcfa, bool push, bool wave)
 #ifndef SFQ_EMIT_WAVES
 #define SFQ_EMIT_WAVES 3
 #endif
-// Emitters dense: above this fraction of a streaming block's particles the emitter kernel
-// writes the block's products with non-temporal stores, and above it for the whole step the
-// next step's emitter pass runs twice the blocks per compute unit (both measured faster at
-// 10-13 % emitters and slower at 2 %).
+// Emitters dense: above this fraction of the step's particles the emitter kernel writes the
+// products with non-temporal stores (measured faster at 10-13 % emitters and slower at 2 %).
 constexpr float DENSE_EMITTER_FRACTION = 0.06f;
 
 // read as the alive flag of tiles that have no alive array
@@ -475,8 +479,9 @@ __device__ __forceinline__ void block_add_counters(unsigned long long* s_cnt,
 #pragma unroll
     for (int k = 0; k < CNT_N; ++k) {
         unsigned long long v = vals[k];
+        if (__ballot(v != 0) == 0) continue;
         for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
-        if (lane_id() == 0 && v) atomicAdd(&s_cnt[k], v);
+        if (lane_id() == 0) atomicAdd(&s_cnt[k], v);
     }
     __syncthreads();
     if (threadIdx.x < CNT_N && s_cnt[threadIdx.x])
@@ -1220,9 +1225,14 @@ __device__ __forceinline__ void stream_block(const StepArgs& A, int b, int G, RT
     for (int k = tid; k < RAD_SIZE; k += STEP_BLOCK) s_rad[k] = g_rad[k];
     for (int k = tid; k < PAIR_SIZE; k += STEP_BLOCK) s_pair[k] = g_pair[k];
     if (tid < CNT_N) s_cnt[tid] = 0;
-    // beyond-LCFA photons take their slots by atomics in the emitter kernel: a step whose
-    // product counts start from zero starts that count here
-    if (BLCFA && A.zero_counts && A.nsets == 0 && b == 0 && tid == 0) A.prod_counts[0] = 0;
+    // the product counts before the step, for the emitter kernel (whose block 0 advances the
+    // counts while the other blocks take their slots); beyond-LCFA photons take theirs by atomics
+    // there: a step whose product counts start from zero starts that count here
+    if (A.nsets == 0 && b == 0 && tid < 3) {
+        reinterpret_cast<unsigned long long*>(A.d_ctl + CTL_BASE)[tid] =
+            A.zero_counts ? 0ull : A.prod_counts[tid];
+        if (BLCFA && A.zero_counts && tid == 0) A.prod_counts[0] = 0;
+    }
     __syncthreads();
 
     unsigned long long c_proc = 0, c_ood = 0;
@@ -1235,17 +1245,17 @@ __device__ __forceinline__ void stream_block(const StepArgs& A, int b, int G, RT
     // every chunk index the counter hands out below N is streamed (or deferred) by the block
     // that got it; G blocks of at most max_chunks >= ceil(N / G) each take all N
     __shared__ int s_chunk;
-    if (tid == 0) s_chunk = (int)atomicAdd(&A.d_ctl[4], 1u);
+    if (tid == 0) s_chunk = (int)atomicAdd(&A.d_ctl[CTL_CHUNK], 1u);
     __syncthreads();
     int c = s_chunk, taken = 0;
     for (; c < A.nchunks && taken < A.max_chunks; ++taken) {
         unsigned nxt = 0;
-        if (tid == 0 && taken + 1 < A.max_chunks) nxt = atomicAdd(&A.d_ctl[4], 1u);
+        if (tid == 0 && taken + 1 < A.max_chunks) nxt = atomicAdd(&A.d_ctl[CTL_CHUNK], 1u);
         // a share whose every particle might emit must fit the slice; otherwise it is left
         // untouched for the deferred-share kernel (no result depends on which wave steps it)
         if (A.q_cap_per_wave - (uint64_t)(sink.nl + sink.np) < (uint64_t)share) {
             if (lane_id() == 0) {
-                const unsigned k = atomicAdd(&A.d_ctl[0], 1u);
+                const unsigned k = atomicAdd(&A.d_ctl[CTL_DEFERRED], 1u);
                 A.d_list[k] = (uint32_t)c * STEP_WAVES + (uint32_t)wv;
             }
         } else {
@@ -1289,99 +1299,207 @@ __global__ __launch_bounds__(STEP_BLOCK, bulk_waves(MIXED, BLCFA, PUSH, WAVE)) v
 }
 
 
-// Emitter pass: the slices of streaming block qb are sampled by emit_split blocks with every
-// lane busy, each taking a contiguous range of their entries: Philox draws, inverse-CDF tables,
-// recoil and products.
-// Product slots: every queued lepton emits one photon and every queued photon converts into
-// one pair (beyond-LCFA rejections are only known here, so that mode takes photon slots by
-// atomics, and steps with per-tile product sets by atomics per set).  A block's slots start at
-// the product counts before the step plus the emitters queued by every earlier streaming
-// block: each block sums those counts itself (one coalesced read of the per-block totals);
-// block 0 adds the step's processed / emitted / converted counters once and the last block out
-// advances the product counts, so no scan kernel runs between the two passes.
+// Emitter pass: Philox draws, inverse-CDF tables, recoil and products for every queued emitter.
+// The step's emitters are numbered, leptons before photons, each in the order of the streaming
+// blocks that queued them, and every wave takes one contiguous range of numbers: each lane finds
+// its entry from the prefix sums of the streaming blocks' counts, which every block makes from
+// their totals (16 bytes per streaming block, read once).  So the waves' work is even and their
+// lanes are full whatever the streaming grid and the emitter fraction were.  (With the slices of
+// each streaming block given to its own emitter blocks, 2048 streaming blocks with 25 emitters
+// each took 2048 emitter blocks, in three rounds of what fits the chip at 25 of 256 lanes:
+// 53 us for the 50k emitters of 2^24 electrons in a uniform field.)
+//
+// Product slots: every queued lepton emits one photon and every queued photon converts into one
+// pair, so an emitter's number is its product's slot, from the product counts before the step
+// (beyond-LCFA rejections are only known here, so that mode takes photon slots by atomics, and
+// steps with per-tile product sets by atomics per set).  Block 0 samples nothing: it adds the
+// step's processed / emitted / converted counters, advances the product counts and stores the
+// observations for sizing the queue, all from what the streaming kernel wrote, so no block waits
+// for another and none counts itself out (an atomic on one word costs the chip about 12 ns each:
+// 2048 blocks took 24 us to count themselves out).
+constexpr int EMIT_ROWS = 2048;  // prefix sums kept in shared memory
+constexpr int EMIT_MIN = 16;     // fewest emitters of a wave: two rounds of the table evaluation
+
 struct EmitShared {
-    unsigned cum[2 * STEP_WAVES + 1];
-    unsigned long long base[3 * STEP_WAVES];
-    unsigned long long tmp[2];
-    uint2 own[STEP_WAVES];
-    unsigned long long b[3];
-    unsigned chunks;  // chunks streamed by the streaming block
+    uint32_t lep[EMIT_ROWS], pho[EMIT_ROWS];  // emitters queued before each group of rows
+    uint32_t wl[STEP_WAVES], wp[STEP_WAVES];
 };
 
-// The emitter work of one block (every thread calls it): part `part` of the entries queued by
-// streaming block qb.
-template <bool MIXED, bool BLCFA, bool LOCAL>
-__device__ __forceinline__ void emit_item(const StepArgs& A, int qb, int part, EmitCounts& C,
-                                          EmitShared& sh)
+// Prefix sums over the streaming blocks' totals, in groups of `gs` blocks (one block per group up
+// to EMIT_ROWS blocks).  The step's emitters number fewer than 2^32: a queue entry takes 48 B.
+__device__ __forceinline__ void emit_prefix(const StepArgs& A, EmitShared& sh, int gs, int ng,
+                                            uint32_t& total_l, uint32_t& total_p)
 {
-    static_assert(LOCAL || !BLCFA, "beyond-LCFA steps use local decisions");
-    const int tid = threadIdx.x;
-    const uint32_t base_step = A.step_ptr ? (uint32_t)*A.step_ptr : A.step;
-    const bool multi = A.nsets > 0;
-    // zeroed counts: the bases are 0 (no separate zeroing kernel before the step)
-    const bool from0 = multi || A.zero_counts;
-    const uint2* qc = reinterpret_cast<const uint2*>(A.q_count);
-    // the emitters queued by the streaming blocks before qb, qb's own slice counts and the
-    // product counts before the step (only the last block out changes them, after every block
-    // has read them here): all loads issued together, one memory round trip
-    unsigned long long pl = 0, pp = 0;
-    {
-        const uint4* qs = reinterpret_cast<const uint4*>(A.q_sbcount);
-#pragma unroll 4
-        for (int k = tid; k < qb; k += STEP_BLOCK) {
-            const uint4 c = qs[k];
-            pl += c.x;
-            pp += c.y;
+    const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
+    const uint4* qs = reinterpret_cast<const uint4*>(A.q_sbcount);
+    constexpr int PER = EMIT_ROWS / STEP_BLOCK;
+    const int gpt = (ng + STEP_BLOCK - 1) / STEP_BLOCK;  // groups of a thread, at most PER
+    uint32_t l[PER], p[PER], sl = 0, sp = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        l[j] = p[j] = 0;
+        const int g = tid * gpt + j;
+        if (j < gpt && g < ng) {
+            const int hi = min((g + 1) * gs, A.grid);
+            for (int r = g * gs; r < hi; ++r) {
+                const uint4 c = qs[r];
+                l[j] += c.x;
+                p[j] += c.y;
+            }
         }
-        const int s_lo = qb * STEP_WAVES;
-        if (tid < STEP_WAVES) sh.own[tid] = qc[s_lo + tid];
-        else if (tid < STEP_WAVES + 3)
-            sh.b[tid - STEP_WAVES] = from0 ? 0ull : A.prod_counts[tid - STEP_WAVES];
-        else if (tid == STEP_WAVES + 3)
-            sh.chunks = qs[qb].z;
+        sl += l[j];
+        sp += p[j];
     }
-    block_sum2(sh.tmp, pl, pp);  // its barriers also publish sh.own and sh.b
-    // qb's slices in order: leptons then photons of slice 0, of slice 1, ...
-    if (tid == 0) {
-        unsigned acc = 0;
-        unsigned long long rl = pl, rp = pp;
-        for (int w = 0; w < STEP_WAVES; ++w) {
-            const uint2 c = sh.own[w];
-            sh.cum[2 * w] = acc;
-            acc += c.x;
-            sh.cum[2 * w + 1] = acc;
-            acc += c.y;
-            // this slice's first photon, electron and positron slots
-            sh.base[3 * w] = multi ? 0ull : sh.b[0] + rl;
-            sh.base[3 * w + 1] = multi ? 0ull : sh.b[1] + rp;
-            sh.base[3 * w + 2] = multi ? 0ull : sh.b[2] + rp;
-            rl += c.x;
-            rp += c.y;
-        }
-        sh.cum[2 * STEP_WAVES] = acc;
+    uint32_t il = sl, ip = sp;  // inclusive over the wave's threads
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t a = __shfl_up(il, o), b = __shfl_up(ip, o);
+        if (lane >= o) { il += a; ip += b; }
+    }
+    if (lane == 63) { sh.wl[wv] = il; sh.wp[wv] = ip; }
+    __syncthreads();
+    uint32_t el = il - sl, ep = ip - sp;
+    total_l = total_p = 0;
+    for (int w = 0; w < STEP_WAVES; ++w) {
+        if (w < wv) { el += sh.wl[w]; ep += sh.wp[w]; }
+        total_l += sh.wl[w];
+        total_p += sh.wp[w];
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int g = tid * gpt + j;
+        if (j < gpt && g < ng) { sh.lep[g] = el; sh.pho[g] = ep; }
+        el += l[j];
+        ep += p[j];
     }
     __syncthreads();
-    const unsigned total = sh.cum[2 * STEP_WAVES];
-    // where the streaming block found emitters dense, the products are written with
-    // non-temporal stores, which are faster there; where they are sparse, ordinary stores are
-    // faster (measured at 2 % and 13 % emitters)
-    const bool nt_prod =
-        (float)total > DENSE_EMITTER_FRACTION * (float)sh.chunks * (float)A.chunk;
-    const unsigned per = (total + A.emit_split - 1) / A.emit_split;
-    const unsigned e_lo = min(total, per * (unsigned)part), e_hi = min(total, e_lo + per);
-    for (unsigned b0e = e_lo; b0e < e_hi; b0e += STEP_BLOCK) {
-        const unsigned e = b0e + tid;
+}
+
+// The queue entry of emitter r of a species: the last streaming block whose prefix is not above
+// r, then the wave of that block whose slice holds it.
+__device__ __forceinline__ uint64_t emit_slot(const StepArgs& A, const EmitShared& sh, int gs,
+                                              int ng, bool pair, uint32_t r)
+{
+    const uint32_t* pre = pair ? sh.pho : sh.lep;
+    int lo = 0, hi = ng - 1;
+    while (__ballot(lo < hi)) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (lo < hi) {
+            if (pre[mid] <= r) lo = mid; else hi = mid - 1;
+        }
+    }
+    uint32_t k = r - pre[lo];
+    int b = lo * gs;
+    if (gs > 1) {
+        const uint4* qs = reinterpret_cast<const uint4*>(A.q_sbcount);
+        const int last = min(b + gs, A.grid) - 1;
+        for (; b < last; ++b) {
+            const uint4 c = qs[b];
+            const uint32_t n = pair ? c.y : c.x;
+            if (k < n) break;
+            k -= n;
+        }
+    }
+    const uint4* qc = reinterpret_cast<const uint4*>(A.q_count) + 2 * (size_t)b;
+    const uint4 c0 = qc[0], c1 = qc[1];  // (leptons, photons) of slices 0, 1 and 2, 3
+    const uint32_t n0 = pair ? c0.y : c0.x, n1 = n0 + (pair ? c0.w : c0.z),
+                   n2 = n1 + (pair ? c1.y : c1.x);
+    const int w = (k >= n0 ? 1 : 0) + (k >= n1 ? 1 : 0) + (k >= n2 ? 1 : 0);
+    k -= w == 0 ? 0u : w == 1 ? n0 : w == 2 ? n1 : n2;
+    const uint64_t sbase = ((uint64_t)b * STEP_WAVES + (uint64_t)w) * A.q_cap_per_wave;
+    return pair ? sbase + A.q_cap_per_wave - 1 - k : sbase + k;
+}
+
+// Block 0's bookkeeping of a step (see above; nothing here depends on the other blocks).
+template <bool BLCFA>
+__device__ __forceinline__ void emit_bookkeeping(const StepArgs& A)
+{
+    __shared__ unsigned s_fmax;
+    __shared__ unsigned long long s_tmp[2];
+    const int tid = threadIdx.x, G = A.grid, S = G * STEP_WAVES;
+    // plain stores to host memory, which the host reads at a later step: the largest emitter
+    // fraction of a wave's shares and the shares deferred (a late or overwritten value only
+    // delays a resize)
+    const uint2* qc = reinterpret_cast<const uint2*>(A.q_count);
+    const uint4* qs = reinterpret_cast<const uint4*>(A.q_sbcount);
+    unsigned long long tl = 0, tp = 0, proc = 0, dummy = 0;
+    float fmax = 0.0f;
+    if (tid == 0) s_fmax = 0;
+#pragma unroll 8
+    for (int sl = tid; sl < S; sl += STEP_BLOCK) {
+        const uint2 c = qc[sl];
+        tl += c.x;
+        tp += c.y;
+        if (A.obs) {
+            // the emitter fraction of the wave's shares: its block's chunks times a share
+            const unsigned chunks = qs[sl / STEP_WAVES].z;
+            const float room = (float)chunks * (float)(A.chunk / STEP_WAVES);
+            if (room > 0.0f) fmax = fmaxf(fmax, (float)(c.x + c.y) / room);
+        }
+    }
+#pragma unroll 4
+    for (int b = tid; b < G; b += STEP_BLOCK) proc += A.q_proc[b];
+    block_sum2(s_tmp, tl, tp);  // its first barrier also publishes s_fmax = 0
+    if (A.obs && fmax > 0.0f) atomicMax(&s_fmax, __float_as_uint(fmax));  // fmax >= 0
+    block_sum2(s_tmp, proc, dummy);
+    if (tid != 0) return;
+    atomicAdd(&A.counters->processed, proc);
+    if (!BLCFA) atomicAdd(&A.counters->emitted, tl);
+    atomicAdd(&A.counters->converted, tp);
+    if (A.nsets == 0) {
+        const unsigned long long* base =
+            reinterpret_cast<const unsigned long long*>(A.d_ctl + CTL_BASE);
+        // beyond-LCFA photons take their slots by atomics from this count
+        if (!BLCFA) A.prod_counts[0] = base[0] + tl;
+        A.prod_counts[1] = base[1] + tp;
+        A.prod_counts[2] = base[2] + tp;
+    }
+    if (A.obs) {
+        A.obs[0] = s_fmax;
+        A.obs[1] = A.d_ctl[CTL_DEFERRED];
+    }
+    A.d_ctl[CTL_CHUNK] = 0;  // the next step's streaming kernel takes chunks from 0 again
+}
+
+template <bool MIXED, bool BLCFA, bool LOCAL>
+__global__ __launch_bounds__(STEP_BLOCK, SFQ_EMIT_WAVES) void emit_kernel(StepArgs A)
+{
+    static_assert(LOCAL || !BLCFA, "beyond-LCFA steps use local decisions");
+    __shared__ unsigned long long s_cnt[CNT_N];
+    __shared__ EmitShared sh;
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0) {
+        emit_bookkeeping<BLCFA>(A);
+        return;
+    }
+    const uint32_t base_step = A.step_ptr ? (uint32_t)*A.step_ptr : A.step;
+    unsigned long long base[3] = {0, 0, 0};
+    if (A.nsets == 0) {
+        const unsigned long long* b =
+            reinterpret_cast<const unsigned long long*>(A.d_ctl + CTL_BASE);
+        base[0] = b[0]; base[1] = b[1]; base[2] = b[2];
+    }
+    if (tid < CNT_N) s_cnt[tid] = 0;
+    const int gs = (A.grid + EMIT_ROWS - 1) / EMIT_ROWS, ng = (A.grid + gs - 1) / gs;
+    uint32_t total_l, total_p;
+    emit_prefix(A, sh, gs, ng, total_l, total_p);
+    const uint64_t total = (uint64_t)total_l + total_p;
+    const uint64_t waves = (uint64_t)(gridDim.x - 1) * STEP_WAVES;
+    // a wave's range of emitters: an even share, whole rounds of the table evaluation (8)
+    const uint64_t per = max((uint64_t)EMIT_MIN, ((total + waves - 1) / waves + 7) & ~(uint64_t)7);
+    const uint64_t first = (uint64_t)(blockIdx.x - 1) * STEP_WAVES * per;
+    if (first >= total) return;
+    const bool nt_prod = (float)total > DENSE_EMITTER_FRACTION * A.n_total;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint64_t e_lo = min(total, first + (uint64_t)wv * per), e_hi = min(total, e_lo + per);
+    EmitCounts C;
+    for (uint64_t b0e = e_lo; b0e < e_hi; b0e += 64) {
+        const uint64_t e = b0e + (uint64_t)lane_id();
         const bool valid = e < e_hi;
-        // this lane's entry: the segment (slice, species) that holds entry e
-        int k = 0;
-#pragma unroll
-        for (int j = 1; j < 2 * STEP_WAVES; ++j)
-            if (e >= sh.cum[j]) k = j;
-        const int w = k >> 1;
-        const bool pair = valid && (k & 1);
-        const unsigned rank = e - sh.cum[k];
-        const uint64_t sbase = ((uint64_t)qb * STEP_WAVES + w) * A.q_cap_per_wave;
-        const uint64_t slot = pair ? sbase + A.q_cap_per_wave - 1 - rank : sbase + rank;
+        const uint32_t ec = (uint32_t)(valid ? e : e_hi - 1);
+        const bool photon = ec >= total_l;
+        const uint32_t r = photon ? ec - total_l : ec;
+        const bool pair = valid && photon;
+        const uint64_t slot = emit_slot(A, sh, gs, ng, photon, r);
         uint32_t i = 0;
         int t = 0;
         double chi = 1.0, gamma = 1.0, px = 0, py = 0, pz = 0, aux = -1.0, aux2 = 0.0;
@@ -1403,104 +1521,13 @@ __device__ __forceinline__ void emit_item(const StepArgs& A, int qb, int part, E
             }
         }
         emit_one<MIXED, BLCFA, LOCAL>(A, valid, pair, i, t, chi, gamma, px, py, pz, quid, aux,
-                                      aux2, base_step, false, sh.base[3 * w] + rank,
-                                      sh.base[3 * w + 1] + rank, sh.base[3 * w + 2] + rank, C,
-                                      nt_prod);
+                                      aux2, base_step, false, base[0] + r, base[1] + r,
+                                      base[2] + r, C, nt_prod);
     }
-}
-
-template <bool MIXED, bool BLCFA, bool LOCAL>
-__global__ __launch_bounds__(STEP_BLOCK, SFQ_EMIT_WAVES) void emit_kernel(StepArgs A)
-{
-    __shared__ unsigned long long s_cnt[CNT_N];
-    __shared__ EmitShared sh;
-    __shared__ unsigned s_fmax;
-    __shared__ int s_last;
-    const int tid = threadIdx.x;
-    const bool multi = A.nsets > 0;
-    const int G = A.grid;
-    if (tid < CNT_N) s_cnt[tid] = 0;
-    if (blockIdx.x == 0) {
-        // Block 0 first adds the step's processed / emitted / converted counters (every queued
-        // lepton emits, every queued photon converts; beyond-LCFA acceptances are counted by
-        // the blocks) and stores the observations for sizing the queue: the largest emitter
-        // fraction of a wave's shares and the shares deferred (plain stores to host memory,
-        // which the host reads at a later step; a late or overwritten value only delays a
-        // resize).  All of it comes from what the streaming kernel wrote.
-        const uint2* qc = reinterpret_cast<const uint2*>(A.q_count);
-        const int S = G * STEP_WAVES;
-        unsigned long long tl = 0, tp = 0, proc = 0, dummy = 0;
-        float fmax = 0.0f;
-        if (tid == 0) s_fmax = 0;
-        const uint4* qs = reinterpret_cast<const uint4*>(A.q_sbcount);
-#pragma unroll 8
-        for (int sl = tid; sl < S; sl += STEP_BLOCK) {
-            const uint2 c = qc[sl];
-            tl += c.x;
-            tp += c.y;
-            if (A.obs) {
-                // the emitter fraction of the wave's shares: its block's chunks times a share
-                const unsigned chunks = qs[sl / STEP_WAVES].z;
-                const float room = (float)chunks * (float)(A.chunk / STEP_WAVES);
-                if (room > 0.0f) fmax = fmaxf(fmax, (float)(c.x + c.y) / room);
-            }
-        }
-#pragma unroll 4
-        for (int b = tid; b < G; b += STEP_BLOCK) proc += A.q_proc[b];
-        block_sum2(sh.tmp, tl, tp);  // its first barrier also publishes s_fmax = 0
-        if (A.obs && fmax > 0.0f) atomicMax(&s_fmax, __float_as_uint(fmax));  // fmax >= 0
-        block_sum2(sh.tmp, proc, dummy);
-        if (tid == 0) {
-            atomicAdd(&A.counters->processed, proc);
-            if (!BLCFA) atomicAdd(&A.counters->emitted, tl);
-            atomicAdd(&A.counters->converted, tp);
-            if (A.obs) {
-                A.obs[0] = s_fmax;
-                A.obs[1] = A.d_ctl[0];
-            }
-            if (A.emit_obs && proc > 0)
-                *A.emit_obs = __float_as_uint((float)(tl + tp) / (float)proc);
-        }
-    }
-    EmitCounts C;
-    emit_item<MIXED, BLCFA, LOCAL>(A, (int)blockIdx.x / A.emit_split,
-                                   (int)blockIdx.x % A.emit_split, C, sh);
     __syncthreads();
     const unsigned long long vals[CNT_N] = {0, BLCFA ? C.emit : 0ull, 0, C.rej, C.ood, C.clamp,
                                             C.over, 0};
     block_add_counters(s_cnt, A.counters, vals);
-    // The last block out advances the product counts.  It reads only what the streaming kernel
-    // wrote, and every block's read of the product counts returned before its count here, so
-    // no memory fence is needed (a device-scope fence would write back the whole L2 of the
-    // block's XCD, in every block).
-    if (tid == 0) {
-        const unsigned done = atomicAdd(&A.d_ctl[3], 1u);
-        s_last = done == gridDim.x - 1;
-    }
-    __syncthreads();
-    if (!s_last) return;
-    if (!multi) {
-        const uint4* qs = reinterpret_cast<const uint4*>(A.q_sbcount);
-        unsigned long long tl = 0, tp = 0;
-#pragma unroll 4
-        for (int b = tid; b < G; b += STEP_BLOCK) {
-            const uint4 c = qs[b];
-            tl += c.x;
-            tp += c.y;
-        }
-        block_sum2(sh.tmp, tl, tp);
-        if (tid == 0) {
-            // beyond-LCFA photons took their slots by atomics from this count (which the
-            // streaming kernel zeroed when the step starts from zero)
-            if (!BLCFA) A.prod_counts[0] = (A.zero_counts ? 0ull : A.prod_counts[0]) + tl;
-            A.prod_counts[1] = (A.zero_counts ? 0ull : A.prod_counts[1]) + tp;
-            A.prod_counts[2] = (A.zero_counts ? 0ull : A.prod_counts[2]) + tp;
-        }
-    }
-    if (tid == 0) {
-        A.d_ctl[3] = 0;
-        A.d_ctl[4] = 0;  // the next step's streaming kernel takes chunks from 0 again
-    }
 }
 
 // The shares the streaming pass deferred (enqueued after the emitter kernel whenever the
@@ -1514,7 +1541,7 @@ __global__ __launch_bounds__(STEP_BLOCK, 1) void defer_kernel(StepArgs A)
     static_assert(LOCAL || !BLCFA, "beyond-LCFA steps use local decisions");
     using RT = typename std::conditional<MIXED, float, double>::type;
     __shared__ unsigned long long s_cnt[CNT_N];
-    const unsigned ndef = A.d_ctl[0];
+    const unsigned ndef = A.d_ctl[CTL_DEFERRED];
     if (ndef == 0) return;  // the same for every block: nothing to step, nothing to clear
     const int tid = threadIdx.x;
     if (tid < CNT_N) s_cnt[tid] = 0;
@@ -1527,7 +1554,7 @@ __global__ __launch_bounds__(STEP_BLOCK, 1) void defer_kernel(StepArgs A)
     unsigned long long c_proc = 0, c_ood = 0;
     for (;;) {
         unsigned u = 0;
-        if (lane_id() == 0) u = atomicAdd(&A.d_ctl[1], 1u);
+        if (lane_id() == 0) u = atomicAdd(&A.d_ctl[CTL_DEFER_NEXT], 1u);
         u = __shfl(u, 0);
         if (u >= ndef) break;
         const uint32_t unit = A.d_list[u];
@@ -1542,11 +1569,11 @@ __global__ __launch_bounds__(STEP_BLOCK, 1) void defer_kernel(StepArgs A)
     // the last block out clears the deferral words (every block is past its last use of them
     // when it counts itself out; no fence: the next kernel sees the stores)
     if (tid == 0) {
-        const unsigned done = atomicAdd(&A.d_ctl[2], 1u);
+        const unsigned done = atomicAdd(&A.d_ctl[CTL_DEFER_DONE], 1u);
         if (done == gridDim.x - 1) {
-            A.d_ctl[0] = 0;
-            A.d_ctl[1] = 0;
-            A.d_ctl[2] = 0;
+            A.d_ctl[CTL_DEFERRED] = 0;
+            A.d_ctl[CTL_DEFER_NEXT] = 0;
+            A.d_ctl[CTL_DEFER_DONE] = 0;
         }
     }
 }
@@ -1731,8 +1758,6 @@ struct sfq_ctx {
     int q_adaptive = 1;
     unsigned* obs_host = nullptr;  // pinned, mapped: the emitter kernel's observations
     unsigned* obs_dev = nullptr;
-    double emit_frac = 0.0;        // the emitter fraction of the last step observed (steps and
-                                   // plan launches): picks the emitter pass's blocks per CU
     // The end of the handle's last step (its own step_done event, or the step's timing event
     // when timing is on): a step on another stream waits for it, since steps share the queue.
     // One event record per step: a staging slot's event is recorded only when the descriptors
@@ -2299,17 +2324,18 @@ static QueueLayout queue_layout(const sfq_ctx* h, const QueueShape& q)
 
 static size_t queue_bytes(const sfq_ctx* h, const QueueShape& q) { return queue_layout(h, q).total; }
 
-// Emitter blocks per streaming block's slices: enough emitter blocks to keep every compute unit
-// busy with the latency-bound emitter pass even when the streaming pass runs few, large blocks;
-// twice as many after a step whose emitters were dense, as each block then has several rounds
-// of emitters to chain.
+// Blocks of the emitter kernel: as many as fit the chip at its registers, 3 per compute unit (so
+// the waves' even shares end together; 6 and 12 per compute unit, in further rounds of blocks,
+// took 46 and 57 us against 36 for the 6 million particles of a pushed plane-wave step, 79 against
+// 66 for 4 million of skewed chi, and the same for 2^25), fewer for steps that cannot fill them,
+// and block 0 for the bookkeeping.  Blocks beyond the step's emitters return at once.
 #ifndef SFQ_EMIT_BPC
-#define SFQ_EMIT_BPC 6
+#define SFQ_EMIT_BPC 3
 #endif
-static int emit_split_for(const sfq_ctx* h, int grid)
+static int emit_grid(const sfq_ctx* h, const StepArgs& A)
 {
-    const int bpc = h->emit_frac > DENSE_EMITTER_FRACTION ? 2 * SFQ_EMIT_BPC : SFQ_EMIT_BPC;
-    return std::max(1, std::min(16, (h->num_cus * bpc) / std::max(1, grid)));
+    const double most = std::ceil((double)A.n_total / (STEP_WAVES * EMIT_MIN));
+    return 1 + (int)std::max(1.0, std::min((double)h->num_cus * SFQ_EMIT_BPC, most));
 }
 
 // The arrays of a queue allocated with the capacities `cap` at `mem`, bound for a step of shape
@@ -2350,7 +2376,6 @@ static void bind_queue(const sfq_ctx* h, StepArgs& A, void* mem, const QueueShap
     A.grid = qs.grid;
     A.max_chunks = qs.max_chunks;
     A.obs = nullptr;
-    A.emit_obs = h->obs_host ? h->obs_dev + 2 : nullptr;
     A.may_defer = qs.may_defer;
 }
 
@@ -2383,8 +2408,12 @@ static void fill_args(const sfq_ctx* h, const sfq_step_desc* desc, StepArgs& A, 
     A.push = desc->push;
     A.zero_counts = desc->zero_product_counts;
     A.wave = 0;
-    for (int t = 0; t < desc->ntiles; ++t)
+    double n_total = 0.0;
+    for (int t = 0; t < desc->ntiles; ++t) {
         if (desc->tiles[t].field_mode == SFQ_FIELDS_PLANE_WAVE) A.wave = 1;
+        n_total += (double)desc->tiles[t].n;
+    }
+    A.n_total = (float)n_total;
 }
 
 // A set of timing events for one step (caller holds h->mu); nullptr when timing is off or the
@@ -2416,7 +2445,7 @@ static void launch_step_kernels(const sfq_ctx* h, const StepArgs& A, int grid, h
     const dim3 g(grid), b(STEP_BLOCK);
     if (pe) (void)hipEventRecord(pe->e[0], st);
     const bool mixed = h->precision == SFQ_MIXED, local = h->decision == SFQ_LOCAL;
-    const dim3 ge(grid * A.emit_split);
+    const dim3 ge(emit_grid(h, A));
 #define SFQ_LAUNCH_FORM(K, G, M, BL, L, X)                                                     \
     do {                                                                                       \
         if (X.push) {                                                                          \
@@ -2551,21 +2580,8 @@ static sfq_status ensure_queue(sfq_ctx* h, const QueueShape& qs, const char* who
 // What the last completed steps observed (the largest emitter fraction of a wave's share,
 // shares deferred): the queue grows to twice the observed fraction, faster after deferrals
 // (caller holds h->mu).  The observation may be a step or two old; sizing never changes results.
-static void observe_emitters(sfq_ctx* h)
-{
-    if (!h->obs_host) return;
-    volatile unsigned* o = h->obs_host;
-    const unsigned fb = o[2];
-    if (!fb) return;
-    float f;
-    memcpy(&f, &fb, sizeof f);
-    h->emit_frac = f;
-    o[2] = 0;
-}
-
 static void adapt_queue(sfq_ctx* h)
 {
-    observe_emitters(h);
     if (!h->q_adaptive || !h->obs_host) return;
     volatile unsigned* o = h->obs_host;
     const unsigned fb = o[0], nd = o[1];
@@ -2771,7 +2787,6 @@ sfq_status sfq_step(sfq_handle h, const sfq_step_desc* desc, void* stream)
     if (desc->nsets > 0) A.sets = (const sfq_product_set*)((char*)S.dev + set_pos);
     bind_queue(h, A, h->d_queue, queue_capacity(h), qs);
     A.obs = h->obs_dev;
-    A.emit_split = emit_split_for(h, qs.grid);
     if (desc->zero_product_counts) enqueue_zero_counts(A, (hipStream_t)stream);
     const ProfEvents* pe = prof_events(h);
     launch_step_kernels(h, A, qs.grid, (hipStream_t)stream, pe);
@@ -2875,8 +2890,6 @@ sfq_status sfq_step_noalloc(sfq_handle h, const sfq_step_desc* desc, void* strea
     A.chunk_off = (const uint32_t*)(sc + off_pos);
     if (desc->nsets > 0) A.sets = (const sfq_product_set*)(sc + set_pos);
     bind_queue(h, A, sc + STAGING_BYTES, qs, qs);
-    observe_emitters(h);
-    A.emit_split = emit_split_for(h, qs.grid);
     if (desc->zero_product_counts) enqueue_zero_counts(A, (hipStream_t)stream);
     launch_step_kernels(h, A, qs.grid, (hipStream_t)stream, nullptr);
     HIP_TRY(h, hipGetLastError());
@@ -2935,8 +2948,6 @@ sfq_status sfq_plan_create(sfq_handle h, const sfq_step_desc* desc, int zero_pro
     p->A.step_ptr = p->d_step;
     if (desc->nsets > 0) p->A.sets = (const sfq_product_set*)((char*)p->d_mem + set_pos);
     bind_queue(h, p->A, (char*)p->d_mem + q_pos, qs, qs);
-    observe_emitters(h);
-    p->A.emit_split = emit_split_for(h, qs.grid);
     *out = p;
     return SFQ_OK;
 }
