@@ -424,30 +424,22 @@ __device__ __forceinline__ void plane_wave_fields(const Wave& w, double a, doubl
     bz = w.k[0] * ey - w.k[1] * ex;
 }
 
+// The last tile t with off[t] <= c (tiles without chunks are skipped), searched by the whole wave:
+// each round reads up to 64 evenly spaced offsets at once and keeps the interval that holds c, so
+// the 4096 tiles a step may have take two dependent loads (a binary search takes twelve).
 __device__ __forceinline__ int find_tile(const uint32_t* off, int ntiles, int c)
 {
-    int lo = 0, hi = ntiles - 1;
-    while (lo < hi) {  // last t with off[t] <= c (tiles without chunks are skipped)
-        const int mid = (lo + hi + 1) >> 1;
-        if ((int)off[mid] <= c) lo = mid; else hi = mid - 1;
+    int lo = 0, n = ntiles;  // the tile is in [lo, lo + n)
+    while (n > 1) {
+        const int gap = (n + 63) >> 6;
+        const int t = lo + lane_id() * gap;
+        const bool in = t < lo + n && (int)off[min(t, ntiles - 1)] <= c;
+        const int k = 63 - __clzll(__ballot(in));  // lane 0 is always in: off[lo] <= c
+        const int last = lo + k * gap;
+        n = min(gap, lo + n - last);
+        lo = last;
     }
     return lo;
-}
-
-// Sum over the block (every thread gets it); s_tmp: at least one word of shared memory, which
-// the caller must not be using.
-__device__ __forceinline__ unsigned long long block_sum(unsigned long long* s_tmp,
-                                                        unsigned long long v)
-{
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
-    __syncthreads();
-    if (threadIdx.x == 0) s_tmp[0] = 0;
-    __syncthreads();
-    if (lane_id() == 0 && v) atomicAdd(&s_tmp[0], v);
-    __syncthreads();
-    const unsigned long long r = s_tmp[0];
-    __syncthreads();
-    return r;
 }
 
 // Sums of two values over the block (every thread gets both); s_tmp: two words of shared
@@ -1207,24 +1199,27 @@ __device__ __forceinline__ void stream_chunk(const StepArgs& A, int c, int tid, 
     }
 }
 
-// The streaming work of block b of G: its waves' queue slices are STEP_WAVES b ... .  Chunks
-// are taken one at a time from a step-wide counter (the next one fetched while the current one
-// streams), at most A.max_chunks per block: blocks that start late or run slow take fewer, so
-// the grid finishes together instead of waiting for its slowest block's fixed share.  (Which
-// block streams a chunk changes no result, only the order of products in their buffers.)
-// s_tmp: two words of shared memory.
+// The streaming work of block b of G: its waves' queue slices are STEP_WAVES b ... .  Block b
+// starts with chunk b; further chunks are taken one at a time from a step-wide counter (the next
+// one fetched while the current one streams), at most A.max_chunks per block: blocks that start
+// late or run slow take fewer, so the grid finishes together instead of waiting for its slowest
+// block's fixed share.  (Which block streams a chunk changes no result, only the order of
+// products in their buffers.)  The counter is one word, at 12 ns an atomic over the chip: a grid
+// whose first chunks came from it too spent 24 us per 1024 blocks on handing out first and next
+// chunks; a step with a chunk per block at most now takes none.
 template <bool MIXED, bool BLCFA, bool LOCAL, bool PUSH, bool WAVE, typename RT>
 __device__ __forceinline__ void stream_block(const StepArgs& A, int b, int G, RT* s_rad,
-                                             RT* s_pair, unsigned long long* s_cnt,
-                                             unsigned long long* s_tmp)
+                                             RT* s_pair)
 {
     static_assert(LOCAL || !BLCFA, "beyond-LCFA steps use local decisions");
+    __shared__ int s_chunk;
+    __shared__ uint32_t s_nl[STEP_WAVES], s_np[STEP_WAVES];
+    __shared__ unsigned long long s_proc[STEP_WAVES];
     const int tid = threadIdx.x;
     const RT* g_rad = MIXED ? (const RT*)A.tb.rad32 : (const RT*)A.tb.rad;
     const RT* g_pair = MIXED ? (const RT*)A.tb.pair32 : (const RT*)A.tb.pair;
     for (int k = tid; k < RAD_SIZE; k += STEP_BLOCK) s_rad[k] = g_rad[k];
     for (int k = tid; k < PAIR_SIZE; k += STEP_BLOCK) s_pair[k] = g_pair[k];
-    if (tid < CNT_N) s_cnt[tid] = 0;
     // the product counts before the step, for the emitter kernel (whose block 0 advances the
     // counts while the other blocks take their slots); beyond-LCFA photons take theirs by atomics
     // there: a step whose product counts start from zero starts that count here
@@ -1242,15 +1237,13 @@ __device__ __forceinline__ void stream_block(const StepArgs& A, int b, int G, RT
     const uint32_t share = (uint32_t)(A.chunk / STEP_WAVES);  // most particles of a wave's share
     const uint32_t base_step = A.step_ptr ? (uint32_t)*A.step_ptr : A.step;
 
-    // every chunk index the counter hands out below N is streamed (or deferred) by the block
-    // that got it; G blocks of at most max_chunks >= ceil(N / G) each take all N
-    __shared__ int s_chunk;
-    if (tid == 0) s_chunk = (int)atomicAdd(&A.d_ctl[CTL_CHUNK], 1u);
-    __syncthreads();
-    int c = s_chunk, taken = 0;
-    for (; c < A.nchunks && taken < A.max_chunks; ++taken) {
+    // every chunk index is streamed (or deferred) by the block that got it; G blocks of at most
+    // max_chunks >= ceil(N / G) each take all N
+    int c = b, taken = 0;
+    for (; c < A.nchunks; ++taken) {
+        const bool more = A.nchunks > G && taken + 1 < A.max_chunks;
         unsigned nxt = 0;
-        if (tid == 0 && taken + 1 < A.max_chunks) nxt = atomicAdd(&A.d_ctl[CTL_CHUNK], 1u);
+        if (more && tid == 0) nxt = atomicAdd(&A.d_ctl[CTL_CHUNK], 1u);
         // a share whose every particle might emit must fit the slice; otherwise it is left
         // untouched for the deferred-share kernel (no result depends on which wave steps it)
         if (A.q_cap_per_wave - (uint64_t)(sink.nl + sink.np) < (uint64_t)share) {
@@ -1262,28 +1255,41 @@ __device__ __forceinline__ void stream_block(const StepArgs& A, int b, int G, RT
             stream_chunk<MIXED, BLCFA, LOCAL, PUSH, WAVE>(A, c, tid, s_rad, s_pair, sink, c_proc,
                                                            c_ood, base_step);
         }
+        if (!more) {
+            ++taken;
+            break;
+        }
         __syncthreads();  // every wave is done with s_chunk
-        if (tid == 0) s_chunk = taken + 1 < A.max_chunks ? (int)nxt : A.nchunks;
+        if (tid == 0) s_chunk = (int)min(nxt, (unsigned)A.nchunks) + G;
         __syncthreads();
         c = s_chunk;
     }
+    // the waves' counts, and the block's totals (what the emitter kernel sums) and its processed
+    // count, go to the queue for the emitter kernel (no global atomic: thousands of blocks adding
+    // to one word serialise); the rare out-of-domain count is added
+    for (int o = 32; o > 0; o >>= 1) c_proc += __shfl_down(c_proc, o);
     if (lane_id() == 0) {
-        A.q_count[2 * slice] = sink.nl;
-        A.q_count[2 * slice + 1] = sink.np;
+        reinterpret_cast<uint2*>(A.q_count)[slice] = make_uint2(sink.nl, sink.np);
+        s_nl[wv] = sink.nl;
+        s_np[wv] = sink.np;
+        s_proc[wv] = c_proc;
     }
-    // the block's totals (what the emitter kernel sums over earlier blocks) and the block's
-    // processed count go to the queue for the emitter kernel (no global atomic:
-    // thousands of blocks adding to one word serialise); the rare out-of-domain count is added
-    unsigned long long tl = lane_id() == 0 ? sink.nl : 0u, tp = lane_id() == 0 ? sink.np : 0u;
-    block_sum2(s_tmp, tl, tp);
-    const unsigned long long proc = block_sum(s_tmp, c_proc);
+    if (__ballot(c_ood != 0)) {
+        for (int o = 32; o > 0; o >>= 1) c_ood += __shfl_down(c_ood, o);
+        if (lane_id() == 0) atomicAdd(&A.counters->out_of_domain, c_ood);
+    }
+    __syncthreads();
     if (tid == 0) {
-        reinterpret_cast<uint4*>(A.q_sbcount)[b] = make_uint4((uint32_t)tl, (uint32_t)tp,
-                                                               (uint32_t)taken, 0u);
+        uint32_t tl = 0, tp = 0;
+        unsigned long long proc = 0;
+        for (int w = 0; w < STEP_WAVES; ++w) {
+            tl += s_nl[w];
+            tp += s_np[w];
+            proc += s_proc[w];
+        }
+        reinterpret_cast<uint4*>(A.q_sbcount)[b] = make_uint4(tl, tp, (uint32_t)taken, 0u);
         A.q_proc[b] = proc;
     }
-    const unsigned long long vals[CNT_N] = {0, 0, 0, 0, c_ood, 0, 0, 0};
-    block_add_counters(s_cnt, A.counters, vals);
 }
 
 template <bool MIXED, bool BLCFA, bool LOCAL, bool PUSH, bool WAVE>
@@ -1292,10 +1298,8 @@ __global__ __launch_bounds__(STEP_BLOCK, bulk_waves(MIXED, BLCFA, PUSH, WAVE)) v
     using RT = typename std::conditional<MIXED, float, double>::type;
     __shared__ RT s_rad[RAD_SIZE];
     __shared__ RT s_pair[PAIR_SIZE];
-    __shared__ unsigned long long s_cnt[CNT_N];
-    __shared__ unsigned long long s_tmp[2];
     stream_block<MIXED, BLCFA, LOCAL, PUSH, WAVE>(A, (int)blockIdx.x, (int)gridDim.x, s_rad,
-                                                   s_pair, s_cnt, s_tmp);
+                                                   s_pair);
 }
 
 
@@ -1773,9 +1777,11 @@ struct sfq_ctx {
     // step with the same descriptors (the same tiles, step after step) reuses that copy
     std::vector<char> last_desc, desc_bytes;
     int last_slot = -1;
-    // launch shape of the step kernel (tunable)
+    // launch shape of the step kernel (tunable); until it is set, the step picks one by its size
+    // and form (auto_shape) and these are only what sfq_get_launch reports
     int blocks_per_cu = 8;
     int chunk = 2048;
+    bool auto_launch = true;
     // kernel timing (sfq_profile_*): events around the two step kernels of each timed step
     int prof = 0;
     std::vector<ProfEvents> prof_used, prof_free;
@@ -2154,6 +2160,7 @@ sfq_status sfq_set_launch(sfq_handle h, int blocks_per_cu, int chunk)
     std::lock_guard<std::mutex> lock(h->mu);
     h->blocks_per_cu = blocks_per_cu;
     h->chunk = chunk;
+    h->auto_launch = false;
     return SFQ_OK;
 }
 
@@ -2170,8 +2177,66 @@ sfq_status sfq_get_launch(sfq_handle h, int* blocks_per_cu, int* chunk)
 // ---------------------------------------------------------------------------------------------
 // Step plumbing shared by sfq_step and the plans
 // ---------------------------------------------------------------------------------------------
+// The launch shape of a step's streaming kernel: the most blocks it runs and the particles of a
+// chunk.
+struct LaunchShape {
+    int max_blocks;
+    int chunk;
+};
+
+static LaunchShape set_shape(const sfq_ctx* h)
+{
+    return {h->num_cus * h->blocks_per_cu, h->chunk};
+}
+
+// The shape of a step of n particles when none is set (times of the streaming kernel on 256
+// compute units).
+//   Up to 8 blocks per compute unit (16 beyond LCFA) of the largest chunk, about 8.4 million
+//   particles: every block streams one chunk, with no counter to ask for a next one, and the
+//   hardware hands out the blocks.  The chunk makes about two blocks per compute unit (twelve
+//   beyond LCFA, whose loop waits longest per particle): shorter ones leave each block's start
+//   (rate tables, descriptors) unpaid, longer ones leave compute units idle.  65,536 particles:
+//   chunks of 256 10 us, of 2048 15; 500,000: 1024 14, 512 15.4, 2048 17.7; 2 million: 4096 37,
+//   2048 40.5; 6 million: 4096 102, 2 x 2048 107, 8 x 2048 114; beyond LCFA 3 million: 1024 107,
+//   2048 115, 4096 129.
+//   Above, resident blocks take chunks in turn: two per compute unit where a lane streams two
+//   adjacent particles (2^25: 2 x 2048 521-525, 3 x 2048 537-543, 4 x 2048 558, 64 x 2048 551),
+//   three in the one-particle loops (local decisions 550, 2 x 2048 603; uniform fields, 2^26, 3 x
+//   4096 861, 2 x 4096 1013, 4 x 4096 888), four for plane-wave tiles, which compute most (2^24:
+//   4 x 4096 232, 3 x 4096 241, 2 x 4096 262) and beyond LCFA (2.3e7: 4 x 2048 718, 3 x 2048 739).
+static LaunchShape auto_shape(const sfq_ctx* h, double n, bool wave, bool uniform)
+{
+    const bool bl = h->blcfa != 0;
+    const int cus = h->num_cus, largest = bl ? 2048 : 4096;
+    if (n <= (double)(bl ? 16 : 8) * cus * largest) {
+        const double even = n / ((bl ? 12.0 : 2.0) * cus);
+        const int unit = even > 512.0 ? 512 : 256;  // two particles per lane: 512 an iteration
+        const int chunk = unit * std::max(1, (int)std::ceil(even / unit));
+        return {1 << 29, std::min(chunk, largest)};
+    }
+    if (bl) return {4 * cus, 2048};
+    if (wave) return {4 * cus, 4096};
+    if (uniform) return {3 * cus, 4096};
+    return {(h->decision == SFQ_LOCAL ? 3 : 2) * cus, 2048};
+}
+
+static LaunchShape launch_shape(const sfq_ctx* h, const sfq_step_desc* desc)
+{
+    if (!h->auto_launch) return set_shape(h);
+    double n = 0.0;
+    bool wave = false, uniform = false;
+    for (int t = 0; t < desc->ntiles; ++t) {
+        n += (double)desc->tiles[t].n;
+        wave |= desc->tiles[t].field_mode == SFQ_FIELDS_PLANE_WAVE;
+        uniform |= desc->tiles[t].field_mode == SFQ_FIELDS_UNIFORM;
+    }
+    return auto_shape(h, n, wave, uniform);
+}
+
+// Checks the descriptor and fills the tiles' chunk offsets for the launch shape `ls`, or, if that
+// has no chunk, for the one it picks there.
 static sfq_status validate_desc(sfq_ctx* h, const sfq_step_desc* desc, std::vector<uint32_t>& off,
-                                int chunk)
+                                LaunchShape& ls)
 {
     if (!desc || !desc->tiles) return fail(h, SFQ_E_ARG, "sfq_step: NULL descriptor");
     if (desc->ntiles <= 0 || desc->ntiles > SFQ_MAX_TILES)
@@ -2188,6 +2253,8 @@ static sfq_status validate_desc(sfq_ctx* h, const sfq_step_desc* desc, std::vect
     if (desc->zero_product_counts != 0 && desc->zero_product_counts != 1)
         return fail(h, SFQ_E_ARG, "sfq_step: zero_product_counts must be 0 or 1");
     const int nt = desc->ntiles;
+    if (ls.chunk == 0) ls = launch_shape(h, desc);
+    const int chunk = ls.chunk;
     off.assign(nt + 1, 0);
     for (int t = 0; t < nt; ++t) {
         const sfq_tile& T = desc->tiles[t];
@@ -2277,11 +2344,11 @@ struct QueueShape {
 // The queue of a step of nchunks chunks.  A wave's slice holds one share of a chunk (what one
 // chunk can add to it) plus the fraction `frac` of every particle of the wave's shares (the
 // expected emitters with headroom), at most all of them: then no share is ever deferred.
-static QueueShape queue_shape(const sfq_ctx* h, int nchunks, int blocks_per_cu, int chunk,
-                              double frac)
+static QueueShape queue_shape(int nchunks, const LaunchShape& ls, double frac)
 {
+    const int chunk = ls.chunk;
     QueueShape q;
-    q.grid = std::max(1, std::min(nchunks, h->num_cus * blocks_per_cu));
+    q.grid = std::max(1, std::min(nchunks, ls.max_blocks));
     q.slices = (uint64_t)q.grid * STEP_WAVES;
     q.max_chunks = max_chunks_per_block(nchunks, q.grid);
     const uint64_t chunks_per_block = (uint64_t)q.max_chunks;
@@ -2603,11 +2670,33 @@ sfq_status sfq_reserve(sfq_handle h, uint64_t max_particles, int max_tiles)
     if (max_tiles < 1 || max_tiles > SFQ_MAX_TILES)
         return fail(h, SFQ_E_ARG, "sfq_reserve: max_tiles in [1, SFQ_MAX_TILES]");
     std::lock_guard<std::mutex> lock(h->mu);
-    const uint64_t nch = (max_particles + h->chunk - 1) / h->chunk + (uint64_t)max_tiles;
-    if (nch >= (1ull << 29)) return fail(h, SFQ_E_CAPACITY, "sfq_reserve: too many particles");
+    // every shape a step within the limits may take: the set one, or those that auto_shape picks
+    // by size (where it changes the chunk or the number of blocks) and form
+    std::vector<std::pair<uint64_t, LaunchShape>> shapes;
+    if (!h->auto_launch) {
+        shapes.push_back({max_particles, set_shape(h)});
+    } else {
+        std::vector<uint64_t> sizes{max_particles};
+        const uint64_t cus = (uint64_t)h->num_cus, per = (h->blcfa ? 12 : 2) * cus;
+        for (uint64_t c = 256; c <= 4096; c += 256) sizes.push_back(per * c);
+        sizes.push_back((h->blcfa ? 16 * 2048 : 8 * 4096) * cus);
+        for (uint64_t n : sizes)
+            if (n <= max_particles)
+                for (int form = 0; form < 3; ++form)
+                    shapes.push_back({n, auto_shape(h, (double)n, form == 1, form == 2)});
+    }
+    QueueShape most{};
+    for (const auto& s : shapes) {
+        const uint64_t nch = (s.first + s.second.chunk - 1) / s.second.chunk + (uint64_t)max_tiles;
+        if (nch >= (1ull << 29)) return fail(h, SFQ_E_CAPACITY, "sfq_reserve: too many particles");
+        const QueueShape q = queue_shape((int)nch, s.second, h->q_frac);
+        most.grid = std::max(most.grid, q.grid);
+        most.slices = std::max(most.slices, q.slices);
+        most.entries = std::max(most.entries, q.entries);
+        most.deferrable = std::max(most.deferrable, q.deferrable);
+    }
     HIP_TRY(h, hipSetDevice(h->device));
-    return ensure_queue(h, queue_shape(h, (int)nch, h->blocks_per_cu, h->chunk, h->q_frac),
-                        "sfq_reserve");
+    return ensure_queue(h, most, "sfq_reserve");
 }
 
 sfq_status sfq_set_queue(sfq_handle h, double expected_fraction, int adaptive)
@@ -2704,10 +2793,10 @@ sfq_status sfq_step(sfq_handle h, const sfq_step_desc* desc, void* stream)
     if (!h) return fail(h, SFQ_E_STATE, "sfq_step: NULL handle");
     std::lock_guard<std::mutex> lock(h->mu);
     std::vector<uint32_t> off;
-    const int chunk = h->chunk;
-    const sfq_status v = validate_desc(h, desc, off, chunk);
+    LaunchShape ls{0, 0};
+    const sfq_status v = validate_desc(h, desc, off, ls);
     if (v != SFQ_OK) return v;
-    const int nt = desc->ntiles;
+    const int nt = desc->ntiles, chunk = ls.chunk;
     HIP_TRY(h, hipSetDevice(h->device));
     // A captured step would keep pointers to memory the handle recycles (a staging slot of the
     // descriptors, the emitter queue, which may be reallocated): graphs are made from plans,
@@ -2734,7 +2823,7 @@ sfq_status sfq_step(sfq_handle h, const sfq_step_desc* desc, void* stream)
         return SFQ_OK;
     }
     adapt_queue(h);
-    const QueueShape qs = queue_shape(h, nchunks, h->blocks_per_cu, chunk, h->q_frac);
+    const QueueShape qs = queue_shape(nchunks, ls, h->q_frac);
     {
         const sfq_status q = ensure_queue(h, qs, "sfq_step");
         if (q != SFQ_OK) return q;
@@ -2812,18 +2901,26 @@ sfq_status sfq_step_noalloc(sfq_handle h, const sfq_step_desc* desc, void* strea
     if (!h->na_scratch || !h->na_host || !h->na_done)
         return fail(h, SFQ_E_STATE, "sfq_step_noalloc: the static scratch of this device could "
                                     "not be set up at sfq_create");
-    // the handle's launch shape, with the chunk halved (results never depend on it) until one
-    // share per slice takes at most half of the queue's room, so that the rest holds emitters
+    // the step's launch shape; if that is not set and its queue (every particle of the step, where
+    // a block streams one chunk) does not fit the room, or if it is set: the handle's shape, with
+    // the chunk halved (results never depend on it) until one share per slice takes at most half
+    // of the queue's room, so that the rest holds emitters
     const size_t room = NOALLOC_SCRATCH_BYTES - STAGING_BYTES;
-    const uint64_t slices = (uint64_t)h->num_cus * (uint64_t)h->blocks_per_cu * STEP_WAVES;
-    int chunk = h->chunk;
-    while (chunk > STEP_BLOCK &&
-           slices * (uint64_t)(chunk / STEP_WAVES) * queue_entry_bytes(h) > room / 2)
-        chunk = std::max(STEP_BLOCK, (chunk / 2) & ~(STEP_BLOCK - 1));
     std::vector<uint32_t> off;
-    const sfq_status v = validate_desc(h, desc, off, chunk);
+    LaunchShape ls{0, 0};
+    sfq_status v = validate_desc(h, desc, off, ls);
     if (v != SFQ_OK) return v;
     const int nt = desc->ntiles;
+    if (!h->auto_launch || queue_bytes(h, queue_shape((int)off[nt], ls, 1.0)) > room) {
+        ls = set_shape(h);
+        const uint64_t slices = (uint64_t)ls.max_blocks * STEP_WAVES;
+        while (ls.chunk > STEP_BLOCK &&
+               slices * (uint64_t)(ls.chunk / STEP_WAVES) * queue_entry_bytes(h) > room / 2)
+            ls.chunk = std::max(STEP_BLOCK, (ls.chunk / 2) & ~(STEP_BLOCK - 1));
+        v = validate_desc(h, desc, off, ls);
+        if (v != SFQ_OK) return v;
+    }
+    const int chunk = ls.chunk;
     HIP_TRY(h, hipSetDevice(h->device));
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     HIP_TRY(h, hipStreamIsCapturing((hipStream_t)stream, &cap));
@@ -2855,7 +2952,7 @@ sfq_status sfq_step_noalloc(sfq_handle h, const sfq_step_desc* desc, void* strea
                                            std::to_string(STAGING_BYTES) + " bytes for them");
     // the queue: the rest of the scratch, its slices as large as it allows (at most the worst
     // case); shares that do not fit are stepped by the deferred-share kernel
-    QueueShape qs = queue_shape(h, nchunks, h->blocks_per_cu, chunk, 1.0);
+    QueueShape qs = queue_shape(nchunks, ls, 1.0);
     const uint64_t worst = qs.cap_per_wave;
     QueueShape probe = qs;
     probe.entries = 0;
@@ -2905,14 +3002,14 @@ sfq_status sfq_plan_create(sfq_handle h, const sfq_step_desc* desc, int zero_pro
     *out = nullptr;
     std::lock_guard<std::mutex> lock(h->mu);
     std::vector<uint32_t> off;
-    const int chunk = h->chunk;
-    const sfq_status v = validate_desc(h, desc, off, chunk);
+    LaunchShape ls{0, 0};
+    const sfq_status v = validate_desc(h, desc, off, ls);
     if (v != SFQ_OK) return v;
-    const int nt = desc->ntiles;
+    const int nt = desc->ntiles, chunk = ls.chunk;
     const int nchunks = (int)off[nt];
     if (nchunks == 0) return fail(h, SFQ_E_ARG, "sfq_plan_create: no particles");
     HIP_TRY(h, hipSetDevice(h->device));
-    const QueueShape qs = queue_shape(h, nchunks, h->blocks_per_cu, chunk, h->q_frac);
+    const QueueShape qs = queue_shape(nchunks, ls, h->q_frac);
     const size_t off_pos = (nt * sizeof(sfq_tile) + 15) & ~(size_t)15;
     const size_t set_pos = (off_pos + (nt + 1) * sizeof(uint32_t) + 15) & ~(size_t)15;
     const size_t step_pos =
