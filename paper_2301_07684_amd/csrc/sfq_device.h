@@ -471,97 +471,121 @@ __device__ __forceinline__ InvReq pair_req(double chi, double u)
     return q;
 }
 
-// Chebyshev polynomial T_m(x) for 0 <= m < 8 by the three-term recurrence
+// Chebyshev polynomials T_{2l}(x) and T_{2l+1}(x) for 0 <= l < 4 by the three-term recurrence
 template <typename T>
-__device__ __forceinline__ T cheb_T(int m, T x)
+__device__ __forceinline__ void cheb_pair(int l, T x, T& even, T& odd)
 {
-    T t0 = T(1), t1 = x, out = m == 0 ? t0 : t1;
+    T t0 = T(1), t1 = x;
+    even = t0;
+    odd = t1;
 #pragma unroll
-    for (int k = 2; k < 8; ++k) {
-        const T t2 = fma(x + x, t1, -t0);
-        out = (m == k) ? t2 : out;
-        t0 = t1;
-        t1 = t2;
+    for (int k = 1; k < 4; ++k) {
+        t0 = fma(x + x, t1, -t0);
+        t1 = fma(x + x, t0, -t1);
+        even = l == k ? t0 : even;
+        odd = l == k ? t1 : odd;
     }
-    return out;
 }
 
-// Position of the k-th set bit (k from 0) of mask, by binary search on popcounts.
-__device__ __forceinline__ int kth_set_bit(unsigned long long mask, int k)
+// A value pushed to lane `to` (a permutation of the wave), and a value read from lane `from`.
+__device__ __forceinline__ int push_lane(int v, int to)
 {
-    int pos = 0;
-#pragma unroll
-    for (int w = 32; w >= 1; w >>= 1) {
-        const int c = __popcll(mask & ((1ull << w) - 1ull));
-        if (k >= c) {
-            k -= c;
-            mask >>= w;
-            pos += w;
-        }
-    }
-    return pos;
+    return __builtin_amdgcn_ds_permute(to << 2, v);
+}
+__device__ __forceinline__ float push_lane(float v, int to)
+{
+    return __int_as_float(push_lane(__float_as_int(v), to));
+}
+__device__ __forceinline__ double push_lane(double v, int to)
+{
+    return __hiloint2double(push_lane(__double2hiint(v), to), push_lane(__double2loint(v), to));
 }
 
-// Cooperative evaluation of an 8 x 8 patch for every lane with `active` set.  In round b the
-// eight lane groups of eight take the next eight active lanes (in lane order): lane m of a
-// group loads column m of that lane's patch (eight lanes read a 64-byte row at once), runs
-// Clenshaw along the r variable and weights by T_m(Xc), and the group sums its columns with
-// xor shuffles.  A wave runs ceil(active lanes / 8) rounds (rounded up to even), so partly
-// filled waves and rare re-evaluations cost only what they use.  Every lane of the wave must
-// call it.
-// With trunc (the same in every lane), the leading INV_TRUNC x INV_TRUNC coefficients: lanes
-// m >= INV_TRUNC of a group load nothing and add zero.
+// v of the lane that DPP control CTRL names (within groups of four lanes: no LDS access)
+template <int CTRL>
+__device__ __forceinline__ float quad_lane(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double quad_lane(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int QUAD_XOR1 = 0xB1, QUAD_XOR2 = 0x4E;
+
+template <typename T> struct Pair;
+template <> struct Pair<double> { typedef double type __attribute__((ext_vector_type(2))); };
+template <> struct Pair<float> { typedef float type __attribute__((ext_vector_type(2))); };
+
+// Columns 2l and 2l + 1 of a patch (l = 0..3), each summed along the r variable by Clenshaw's
+// recurrence over its leading N rows and weighted with T_{2l}(xc), T_{2l+1}(xc): their sum.
+template <int N, typename T>
+__device__ __forceinline__ T patch_columns(const T* patch, int l, T xr, T xc, bool second)
+{
+    using V = typename Pair<T>::type;
+    const V* c = reinterpret_cast<const V*>(patch) + l;
+    T col0[N], col1[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const V v = c[i * (INV_NC / 2)];
+        col0[i] = v.x;
+        col1[i] = v.y;
+    }
+    T even, odd;
+    cheb_pair(l, xc, even, odd);
+    const T a = clenshaw<N>(col0, xr) * even;
+    const T b = second ? clenshaw<N>(col1, xr) * odd : T(0);
+    {
+#pragma clang fp contract(off)
+        return a + b;
+    }
+}
+
+// Cooperative evaluation of an 8 x 8 patch for every lane with `active` set.  The requests are
+// moved to the low lanes of the wave (one permutation); in round b the sixteen lane groups of
+// four take requests 16 b .. 16 b + 15: lane l of a group reads columns 2l and 2l + 1 of the
+// patch (16 bytes a row, the four lanes a row's 64 bytes), runs Clenshaw along the r variable,
+// weights by T_m(Xc), and the group adds its columns with two lane moves.  Partly filled waves
+// and rare re-evaluations cost only the rounds they use.  Every lane of the wave must call it.
+// What bounds it is instructions, then the vector L1 (512 bytes a patch): with eight lanes a
+// patch, one column each, twice the rounds, each with its own request moves and polynomials,
+// reductions through LDS and a search for the k-th active lane, 10^6 photon energies took 43 us
+// instead of 29 (FP64; 4 10^6: 179 and 117, of which 42 are the table reads: 75 with one patch).
+// With trunc (the same in every lane), the leading INV_TRUNC x INV_TRUNC coefficients: the
+// columns beyond add zero.
 template <typename T>
 __device__ __forceinline__ T coop_patch_eval(const T* table, int patch, T Xr, T Xc, bool active,
                                              bool trunc)
 {
-    const int L = __lane_id();
-    const int g = L >> 3, m = L & 7;
+    const int L = __lane_id(), l = L & 3;
     const unsigned long long mask = __ballot(active);
     const int cnt = __popcll(mask);
     const int rank = __popcll(mask & ((1ull << L) - 1ull));
-    const int first = cnt ? kth_set_bit(mask, 0) : 0;
+    if (mask != ~0ull) {  // the inactive lanes go behind the active ones
+        const int to = active ? rank : cnt + L - rank;
+        patch = push_lane(patch, to);
+        Xr = push_lane(Xr, to);
+        Xc = push_lane(Xc, to);
+    }
     T result = T(0);
-    // two rounds per trip, so that two column loads are in flight together
 #pragma unroll 1
-    for (int b = 0; 8 * b < cnt; b += 2) {
-        const int k0 = 8 * b + g, k1 = k0 + 8;
-        const int s0 = k0 < cnt ? kth_set_bit(mask, k0) : first;  // spare groups redo a lane
-        const int s1 = k1 < cnt ? kth_set_bit(mask, k1) : first;
-        const int p0 = __shfl(patch, s0), p1 = __shfl(patch, s1);
-        const T xr0 = __shfl(Xr, s0), xc0 = __shfl(Xc, s0);
-        const T xr1 = __shfl(Xr, s1), xc1 = __shfl(Xc, s1);
-        const T* c0 = table + (size_t)p0 * INV_PATCH + m;
-        const T* c1 = table + (size_t)p1 * INV_PATCH + m;
-        T v0 = T(0), v1 = T(0);
-        if (!trunc) {
-            T col0[INV_NR], col1[INV_NR];
-#pragma unroll
-            for (int i = 0; i < INV_NR; ++i) {
-                col0[i] = c0[i * INV_NC];
-                col1[i] = c1[i * INV_NC];
-            }
-            v0 = clenshaw<INV_NR>(col0, xr0) * cheb_T(m, xc0);
-            v1 = clenshaw<INV_NR>(col1, xr1) * cheb_T(m, xc1);
-        } else if (m < INV_TRUNC) {
-            T col0[INV_TRUNC], col1[INV_TRUNC];
-#pragma unroll
-            for (int i = 0; i < INV_TRUNC; ++i) {
-                col0[i] = c0[i * INV_NC];
-                col1[i] = c1[i * INV_NC];
-            }
-            v0 = clenshaw<INV_TRUNC>(col0, xr0) * cheb_T(m, xc0);
-            v1 = clenshaw<INV_TRUNC>(col1, xr1) * cheb_T(m, xc1);
+    for (int b = 0; 16 * b < cnt; ++b) {
+        const int k = 16 * b + (L >> 2);
+        const int p = __shfl(patch, k);
+        const T xr = __shfl(Xr, k), xc = __shfl(Xc, k);
+        T v = T(0);
+        if (k < cnt) {
+            const T* c = table + (size_t)p * INV_PATCH;
+            if (!trunc) v = patch_columns<INV_NR>(c, l, xr, xc, true);
+            else if (2 * l < INV_TRUNC)
+                v = patch_columns<INV_TRUNC>(c, l, xr, xc, 2 * l + 1 < INV_TRUNC);
         }
-        v0 += __shfl_xor(v0, 1);
-        v1 += __shfl_xor(v1, 1);
-        v0 += __shfl_xor(v0, 2);
-        v1 += __shfl_xor(v1, 2);
-        v0 += __shfl_xor(v0, 4);
-        v1 += __shfl_xor(v1, 4);
-        const T got0 = __shfl(v0, (rank & 7) << 3), got1 = __shfl(v1, (rank & 7) << 3);
-        if (active && (rank >> 3) == b) result = got0;
-        if (active && (rank >> 3) == b + 1) result = got1;
+        v += quad_lane<QUAD_XOR1>(v);
+        v += quad_lane<QUAD_XOR2>(v);
+        const T got = __shfl(v, (rank & 15) << 2);
+        if (active && (rank >> 4) == b) result = got;
     }
     return result;
 }
