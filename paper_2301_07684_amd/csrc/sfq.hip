@@ -82,8 +82,8 @@ struct StepArgs {
     double* q_aux;              // beyond-LCFA tau/tau_C for the threshold (negative: LCFA)
     double* q_aux2;             // beyond-LCFA: gamma of the pushed momentum minus gamma^{(n)}
     uint32_t* q_count;          // [2 slices]: lepton and photon emitters queued in each slice
-    uint32_t* q_sbcount;        // [4 grid]: per streaming block its slices' two sums, the chunks
-                                // it took and a spare word
+    uint32_t* q_sbcount;        // [2 grid]: per streaming block its slices' two sums
+    uint32_t* q_chunks;         // [grid]: the chunks each streaming block took
     unsigned long long* q_proc; // [grid]: particles processed by each block of the streaming pass
     uint64_t q_cap_per_wave;    // entries of one slice
     // Shares that did not fit: a wave whose slice could not take every particle of its share of
@@ -285,18 +285,21 @@ __device__ __forceinline__ unsigned long long wave_reserve(unsigned long long* c
     return base + (unsigned long long)__popcll(below);
 }
 
-// Slots in per-owner product buffers: the lanes of a wave that want a slot are grouped by their
-// set index and the first lane of each group takes the group's slots.  The groups' atomics are
-// issued together (one memory round trip however many sets the wave's lanes belong to; one after
-// the other, they made the emitter pass of a six-simulation batch of 3 million particles 65 us
-// instead of 58 at 2 x 2048, and 90 instead of 66 at 4 x 512).
+// Slots in per-owner product buffers for a wave's emitters: a lane with a photon (pair == false)
+// takes one of its set's photon slots, a lane with a pair one electron and one positron slot.  The
+// lanes are grouped by set and kind; the first lane of each group takes the group's slots.  All
+// atomics of the wave are issued together: one memory round trip however many sets its lanes
+// belong to (one set after the other and one species after the other, the emitter pass of a
+// six-simulation batch of 3 million particles took 90 us at 4 x 512, 66 with the sets together).
 // Every lane of the wave must call this (the loop is wave-uniform).
-__device__ __forceinline__ unsigned long long keyed_reserve(const sfq_product_set* sets,
-                                                            int species, int key, bool want)
+__device__ __forceinline__ void set_reserve(const sfq_product_set* sets, int set, bool want,
+                                            bool pair, unsigned long long& first,
+                                            unsigned long long& second)
 {
+    first = second = 0;
     unsigned long long pending = __ballot(want);
-    if (pending == 0) return 0;
-    const int lane = lane_id();
+    if (pending == 0) return;
+    const int lane = lane_id(), key = 2 * set + (pair ? 1 : 0);
     unsigned long long group = 0;
     while (pending) {
         const int lk = __builtin_amdgcn_readlane(key, __ffsll((long long)pending) - 1);
@@ -305,11 +308,15 @@ __device__ __forceinline__ unsigned long long keyed_reserve(const sfq_product_se
         pending &= ~m;
     }
     const int leader = want ? __ffsll((long long)group) - 1 : lane;
-    unsigned long long base = 0;
-    if (want && lane == leader)
-        base = atomicAdd(&sets[key].product_counts[species], (unsigned long long)__popcll(group));
-    base = __shfl(base, leader);
-    return base + (unsigned long long)__popcll(group & ((1ull << lane) - 1ull));
+    if (want && lane == leader) {
+        unsigned long long* counts = sets[set].product_counts;
+        const unsigned long long n = (unsigned long long)__popcll(group);
+        first = atomicAdd(&counts[pair ? 1 : 0], n);
+        if (pair) second = atomicAdd(&counts[2], n);
+    }
+    const unsigned long long below = (unsigned long long)__popcll(group & ((1ull << lane) - 1ull));
+    first = __shfl(first, leader) + below;
+    second = __shfl(second, leader) + below;
 }
 
 // =============================================================================================
@@ -608,26 +615,24 @@ __device__ __forceinline__ void emit_one(const StepArgs& A, bool valid, bool pai
         }
         C.ood += ood ? 1 : 0;
     }
-    {
-        unsigned long long k;
-        if (multi) k = keyed_reserve(A.sets, 0, pset, want_ph);
-        else k = (BLCFA || atomic_slots) ? wave_reserve(&A.prod_counts[0], want_ph) : k_ph;
-        if (want_ph) {
-            const sfq_products P = multi ? A.sets[pset].photons : A.prod[0];
-            if (k < P.capacity) {
-                store_product(P, k, pgx, pgy, pgz, tau_a, uid_a, parent, nt_prod);
-            } else {
-                ++C.over;
-            }
-        }
-    }
     unsigned long long ke = k_el, kp = k_po;
     if (multi) {
-        ke = keyed_reserve(A.sets, 1, pset, want_pair);
-        kp = keyed_reserve(A.sets, 2, pset, want_pair);
-    } else if (atomic_slots) {
-        ke = wave_reserve(&A.prod_counts[1], want_pair);
-        kp = wave_reserve(&A.prod_counts[2], want_pair);
+        set_reserve(A.sets, pset, want_ph || want_pair, want_pair, ke, kp);
+        k_ph = ke;
+    } else {
+        if (BLCFA || atomic_slots) k_ph = wave_reserve(&A.prod_counts[0], want_ph);
+        if (atomic_slots) {
+            ke = wave_reserve(&A.prod_counts[1], want_pair);
+            kp = wave_reserve(&A.prod_counts[2], want_pair);
+        }
+    }
+    if (want_ph) {
+        const sfq_products P = multi ? A.sets[pset].photons : A.prod[0];
+        if (k_ph < P.capacity) {
+            store_product(P, k_ph, pgx, pgy, pgz, tau_a, uid_a, parent, nt_prod);
+        } else {
+            ++C.over;
+        }
     }
     if (want_pair) {
         const sfq_products E = multi ? A.sets[pset].electrons : A.prod[1];
@@ -1287,7 +1292,8 @@ __device__ __forceinline__ void stream_block(const StepArgs& A, int b, int G, RT
             tp += s_np[w];
             proc += s_proc[w];
         }
-        reinterpret_cast<uint4*>(A.q_sbcount)[b] = make_uint4(tl, tp, (uint32_t)taken, 0u);
+        reinterpret_cast<uint2*>(A.q_sbcount)[b] = make_uint2(tl, tp);
+        A.q_chunks[b] = (uint32_t)taken;
         A.q_proc[b] = proc;
     }
 }
@@ -1307,7 +1313,7 @@ __global__ __launch_bounds__(STEP_BLOCK, bulk_waves(MIXED, BLCFA, PUSH, WAVE)) v
 // The step's emitters are numbered, leptons before photons, each in the order of the streaming
 // blocks that queued them, and every wave takes one contiguous range of numbers: each lane finds
 // its entry from the prefix sums of the streaming blocks' counts, which every block makes from
-// their totals (16 bytes per streaming block, read once).  So the waves' work is even and their
+// their totals (8 bytes per streaming block, read once).  So the waves' work is even and their
 // lanes are full whatever the streaming grid and the emitter fraction were.  (With the slices of
 // each streaming block given to its own emitter blocks, 2048 streaming blocks with 25 emitters
 // each took 2048 emitter blocks, in three rounds of what fits the chip at 25 of 256 lanes:
@@ -1321,83 +1327,127 @@ __global__ __launch_bounds__(STEP_BLOCK, bulk_waves(MIXED, BLCFA, PUSH, WAVE)) v
 // observations for sizing the queue, all from what the streaming kernel wrote, so no block waits
 // for another and none counts itself out (an atomic on one word costs the chip about 12 ns each:
 // 2048 blocks took 24 us to count themselves out).
-constexpr int EMIT_ROWS = 2048;  // prefix sums kept in shared memory
-constexpr int EMIT_MIN = 16;     // fewest emitters of a wave: two rounds of the table evaluation
+constexpr int EMIT_ROWS = 4096;  // prefix sums kept in shared memory (a power of four)
+constexpr int EMIT_MIN = 16;     // fewest emitters of a wave: one round of the table evaluation
 
 struct EmitShared {
-    uint32_t lep[EMIT_ROWS], pho[EMIT_ROWS];  // emitters queued before each group of rows
+    uint32_t lep[EMIT_ROWS], pho[EMIT_ROWS];  // emitters queued before each row
     uint32_t wl[STEP_WAVES], wp[STEP_WAVES];
 };
 
-// Prefix sums over the streaming blocks' totals, in groups of `gs` blocks (one block per group up
-// to EMIT_ROWS blocks).  The step's emitters number fewer than 2^32: a queue entry takes 48 B.
-__device__ __forceinline__ void emit_prefix(const StepArgs& A, EmitShared& sh, int gs, int ng,
+// Inclusive sum over the lanes up to this one, by lane moves within the vector registers (rows of
+// 16 lanes, then the rows' last lanes): no LDS round trips.
+__device__ __forceinline__ uint32_t wave_inclusive(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return x;
+}
+
+// The rows of the prefix sums: the streaming blocks, in groups of `group` if they are more than
+// EMIT_ROWS.
+struct EmitRows {
+    int rows, group;
+    int top4;  // the power of four that covers the rows
+};
+
+__device__ __forceinline__ EmitRows emit_rows(int grid)
+{
+    EmitRows R;
+    R.group = (grid + EMIT_ROWS - 1) / EMIT_ROWS;
+    R.rows = (grid + R.group - 1) / R.group;
+    R.top4 = 1;
+    while (R.top4 < R.rows) R.top4 <<= 2;
+    return R;
+}
+
+// Prefix sums over the rows' counts; rows rows .. top4 - 1 are put out of reach.  Wave w sums the
+// w-th quarter, 64 rows at a time: whole lines read, all reads in flight together, neighbouring
+// words of shared memory.  (A few rows next to each other per thread: 8 us for 2900 rows, for the
+// bank conflicts, or, read directly, for a line per lane and read.)
+// The step's emitters number fewer than 2^32: a queue entry takes 48 B.
+__device__ __forceinline__ void emit_prefix(const StepArgs& A, EmitShared& sh, const EmitRows& R,
                                             uint32_t& total_l, uint32_t& total_p)
 {
-    const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
-    const uint4* qs = reinterpret_cast<const uint4*>(A.q_sbcount);
+    const int wv = threadIdx.x >> 6;
+    const uint2* qs = reinterpret_cast<const uint2*>(A.q_sbcount);
     constexpr int PER = EMIT_ROWS / STEP_BLOCK;
-    const int gpt = (ng + STEP_BLOCK - 1) / STEP_BLOCK;  // groups of a thread, at most PER
-    uint32_t l[PER], p[PER], sl = 0, sp = 0;
+    const int per = (R.top4 + STEP_BLOCK - 1) / STEP_BLOCK;  // rounds of 64 rows, at most PER
+    const int first = wv * per * 64 + lane_id();
+    uint2 c[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        l[j] = p[j] = 0;
-        const int g = tid * gpt + j;
-        if (j < gpt && g < ng) {
-            const int hi = min((g + 1) * gs, A.grid);
-            for (int r = g * gs; r < hi; ++r) {
-                const uint4 c = qs[r];
-                l[j] += c.x;
-                p[j] += c.y;
+        c[j] = make_uint2(0, 0);
+        if (j < per && first + j * 64 < R.rows) c[j] = qs[(first + j * 64) * R.group];
+    }
+    for (int k = 1; k < R.group; ++k) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int b = (first + j * 64) * R.group + k;
+            if (j < per && first + j * 64 < R.rows && b < A.grid) {
+                c[j].x += qs[b].x;
+                c[j].y += qs[b].y;
             }
         }
-        sl += l[j];
-        sp += p[j];
     }
-    uint32_t il = sl, ip = sp;  // inclusive over the wave's threads
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t a = __shfl_up(il, o), b = __shfl_up(ip, o);
-        if (lane >= o) { il += a; ip += b; }
+    uint32_t sl = 0, sp = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (j < per) {
+            sl += c[j].x;
+            sp += c[j].y;
+            sh.lep[first + j * 64] = c[j].x;
+            sh.pho[first + j * 64] = c[j].y;
+        }
     }
-    if (lane == 63) { sh.wl[wv] = il; sh.wp[wv] = ip; }
+    sl = wave_inclusive(sl);
+    sp = wave_inclusive(sp);
+    if (lane_id() == 63) { sh.wl[wv] = sl; sh.wp[wv] = sp; }
     __syncthreads();
-    uint32_t el = il - sl, ep = ip - sp;
+    uint32_t el = 0, ep = 0;
     total_l = total_p = 0;
     for (int w = 0; w < STEP_WAVES; ++w) {
         if (w < wv) { el += sh.wl[w]; ep += sh.wp[w]; }
         total_l += sh.wl[w];
         total_p += sh.wp[w];
     }
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int g = tid * gpt + j;
-        if (j < gpt && g < ng) { sh.lep[g] = el; sh.pho[g] = ep; }
-        el += l[j];
-        ep += p[j];
+#pragma unroll 1
+    for (int j = 0; j < per; ++j) {
+        const int g = first + j * 64;
+        const uint32_t cl = sh.lep[g], cp = sh.pho[g];
+        const uint32_t il = wave_inclusive(cl), ip = wave_inclusive(cp);
+        sh.lep[g] = g < R.rows ? el + il - cl : ~0u;
+        sh.pho[g] = g < R.rows ? ep + ip - cp : ~0u;
+        el += (uint32_t)__builtin_amdgcn_readlane((int)il, 63);
+        ep += (uint32_t)__builtin_amdgcn_readlane((int)ip, 63);
     }
     __syncthreads();
 }
 
-// The queue entry of emitter r of a species: the last streaming block whose prefix is not above
-// r, then the wave of that block whose slice holds it.
-__device__ __forceinline__ uint64_t emit_slot(const StepArgs& A, const EmitShared& sh, int gs,
-                                              int ng, bool pair, uint32_t r)
+// The queue entry of emitter r of a species: the last row whose prefix is not above r (a search
+// over quarters: three reads at once, four rounds for 256 rows), the streaming block, and the
+// slice within it.  (A search over halves with a vote a round took a lane 2.3 us to its entry;
+// this takes 1.4.)
+__device__ __forceinline__ uint64_t emit_slot(const StepArgs& A, const EmitShared& sh,
+                                              const EmitRows& R, bool pair, uint32_t r)
 {
     const uint32_t* pre = pair ? sh.pho : sh.lep;
-    int lo = 0, hi = ng - 1;
-    while (__ballot(lo < hi)) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (lo < hi) {
-            if (pre[mid] <= r) lo = mid; else hi = mid - 1;
-        }
+    int g = 0;
+    for (int q = R.top4 >> 2; q > 0; q >>= 2) {
+        const uint32_t a = pre[g + q], b = pre[g + 2 * q], c = pre[g + 3 * q];
+        g += (a <= r ? q : 0) + (b <= r ? q : 0) + (c <= r ? q : 0);
     }
-    uint32_t k = r - pre[lo];
-    int b = lo * gs;
-    if (gs > 1) {
-        const uint4* qs = reinterpret_cast<const uint4*>(A.q_sbcount);
-        const int last = min(b + gs, A.grid) - 1;
+    uint32_t k = r - pre[g];
+    int b = g * R.group;
+    if (R.group > 1) {
+        const uint2* qs = reinterpret_cast<const uint2*>(A.q_sbcount);
+        const int last = min(b + R.group, A.grid) - 1;
         for (; b < last; ++b) {
-            const uint4 c = qs[b];
+            const uint2 c = qs[b];
             const uint32_t n = pair ? c.y : c.x;
             if (k < n) break;
             k -= n;
@@ -1424,7 +1474,6 @@ __device__ __forceinline__ void emit_bookkeeping(const StepArgs& A)
     // fraction of a wave's shares and the shares deferred (a late or overwritten value only
     // delays a resize)
     const uint2* qc = reinterpret_cast<const uint2*>(A.q_count);
-    const uint4* qs = reinterpret_cast<const uint4*>(A.q_sbcount);
     unsigned long long tl = 0, tp = 0, proc = 0, dummy = 0;
     float fmax = 0.0f;
     if (tid == 0) s_fmax = 0;
@@ -1435,7 +1484,7 @@ __device__ __forceinline__ void emit_bookkeeping(const StepArgs& A)
         tp += c.y;
         if (A.obs) {
             // the emitter fraction of the wave's shares: its block's chunks times a share
-            const unsigned chunks = qs[sl / STEP_WAVES].z;
+            const unsigned chunks = A.q_chunks[sl / STEP_WAVES];
             const float room = (float)chunks * (float)(A.chunk / STEP_WAVES);
             if (room > 0.0f) fmax = fmaxf(fmax, (float)(c.x + c.y) / room);
         }
@@ -1483,13 +1532,16 @@ __global__ __launch_bounds__(STEP_BLOCK, SFQ_EMIT_WAVES) void emit_kernel(StepAr
         base[0] = b[0]; base[1] = b[1]; base[2] = b[2];
     }
     if (tid < CNT_N) s_cnt[tid] = 0;
-    const int gs = (A.grid + EMIT_ROWS - 1) / EMIT_ROWS, ng = (A.grid + gs - 1) / gs;
+    const EmitRows R = emit_rows(A.grid);
     uint32_t total_l, total_p;
-    emit_prefix(A, sh, gs, ng, total_l, total_p);
+    emit_prefix(A, sh, R, total_l, total_p);
     const uint64_t total = (uint64_t)total_l + total_p;
     const uint64_t waves = (uint64_t)(gridDim.x - 1) * STEP_WAVES;
     // a wave's range of emitters: an even share, whole rounds of the table evaluation (8)
-    const uint64_t per = max((uint64_t)EMIT_MIN, ((total + waves - 1) / waves + 7) & ~(uint64_t)7);
+    // where the waves take product slots by atomics, on few words at 12 ns each, they take whole
+    // waves' worth (a six-simulation batch: 20 of the pass's 31 us fell to 21 in all)
+    const uint64_t least = BLCFA || A.nsets > 0 ? 64 : EMIT_MIN;
+    const uint64_t per = max(least, ((total + waves - 1) / waves + 7) & ~(uint64_t)7);
     const uint64_t first = (uint64_t)(blockIdx.x - 1) * STEP_WAVES * per;
     if (first >= total) return;
     const bool nt_prod = (float)total > DENSE_EMITTER_FRACTION * A.n_total;
@@ -1503,7 +1555,7 @@ __global__ __launch_bounds__(STEP_BLOCK, SFQ_EMIT_WAVES) void emit_kernel(StepAr
         const bool photon = ec >= total_l;
         const uint32_t r = photon ? ec - total_l : ec;
         const bool pair = valid && photon;
-        const uint64_t slot = emit_slot(A, sh, gs, ng, photon, r);
+        const uint64_t slot = emit_slot(A, sh, R, photon, r);
         uint32_t i = 0;
         int t = 0;
         double chi = 1.0, gamma = 1.0, px = 0, py = 0, pz = 0, aux = -1.0, aux2 = 0.0;
@@ -2382,7 +2434,7 @@ static QueueLayout queue_layout(const sfq_ctx* h, const QueueShape& q)
     QueueLayout L;
     L.count = 256;
     L.sbcount = al(L.count + 8 * q.slices);
-    L.proc = al(L.sbcount + 16 * (size_t)q.grid);
+    L.proc = al(L.sbcount + 12 * (size_t)q.grid);
     L.dlist = al(L.proc + 8 * (size_t)q.grid);
     L.soa = al(L.dlist + 4 * q.deferrable);
     L.total = L.soa + q.entries * queue_entry_bytes(h);
@@ -2437,6 +2489,7 @@ static void bind_queue(const sfq_ctx* h, StepArgs& A, void* mem, const QueueShap
     A.d_ctl = (unsigned*)base;
     A.q_count = (uint32_t*)(base + L.count);
     A.q_sbcount = (uint32_t*)(base + L.sbcount);
+    A.q_chunks = A.q_sbcount + 2 * (size_t)cap.grid;
     A.q_proc = (unsigned long long*)(base + L.proc);
     A.d_list = (uint32_t*)(base + L.dlist);
     A.q_cap_per_wave = qs.cap_per_wave;

@@ -71,6 +71,11 @@ struct Draw {
     uint64_t a, b;
 };
 
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 __device__ __forceinline__ Draw philox_draw(uint64_t seed, uint64_t uid, uint32_t step,
                                             uint32_t purpose)
 {
@@ -78,10 +83,12 @@ __device__ __forceinline__ Draw philox_draw(uint64_t seed, uint64_t uid, uint32_
     uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
 #pragma unroll
     for (int round = 0; round < 10; ++round) {
-        const uint32_t lo0 = 0xD2511F53u * x0, hi0 = __umulhi(0xD2511F53u, x0);
-        const uint32_t lo1 = 0xCD9E8D57u * x2, hi1 = __umulhi(0xCD9E8D57u, x2);
-        const uint32_t y0 = hi1 ^ x1 ^ k0, y2 = hi0 ^ x3 ^ k1;
-        x0 = y0; x1 = lo1; x2 = y2; x3 = lo0;
+        // one quarter-rate multiplication gives both halves of a product (v_mad_u64_u32, where
+        // separate low and high products take two), one operation the three-way exclusive or
+        const uint64_t p0 = (uint64_t)0xD2511F53u * x0, p1 = (uint64_t)0xCD9E8D57u * x2;
+        const uint32_t y0 = xor3((uint32_t)(p1 >> 32), x1, k0),
+                       y2 = xor3((uint32_t)(p0 >> 32), x3, k1);
+        x0 = y0; x1 = (uint32_t)p1; x2 = y2; x3 = (uint32_t)p0;
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
