@@ -2310,28 +2310,28 @@ static sfq_status validate_desc(sfq_ctx* h, const sfq_step_desc* desc, std::vect
     off.assign(nt + 1, 0);
     for (int t = 0; t < nt; ++t) {
         const sfq_tile& T = desc->tiles[t];
-        const std::string tn = " (tile " + std::to_string(t) + ")";
+        const auto tn = [t] { return " (tile " + std::to_string(t) + ")"; };
         if (T.species < 0 || T.species > 2)
-            return fail(h, SFQ_E_ARG, "sfq_step: bad tile species" + tn);
+            return fail(h, SFQ_E_ARG, "sfq_step: bad tile species" + tn());
         if (T.field_mode < SFQ_FIELDS_ARRAYS || T.field_mode > SFQ_FIELDS_PLANE_WAVE)
-            return fail(h, SFQ_E_ARG, "sfq_step: bad field_mode" + tn);
+            return fail(h, SFQ_E_ARG, "sfq_step: bad field_mode" + tn());
         if (desc->nsets == 0 ? T.product_set != 0
                              : (T.product_set < 0 || T.product_set >= desc->nsets))
-            return fail(h, SFQ_E_ARG, "sfq_step: product set index out of range" + tn);
+            return fail(h, SFQ_E_ARG, "sfq_step: product set index out of range" + tn());
         if (T.n >= (1ull << 32))
             return fail(h, SFQ_E_CAPACITY, "sfq_step: tile larger than 2^32 - 1 particles");
         const bool photon = T.species == SFQ_PHOTON;
         const bool bl = h->blcfa && !photon;
         if (T.n > 0) {
             if (!T.px || !T.py || !T.pz || !T.uid)
-                return fail(h, SFQ_E_ARG, "sfq_step: NULL momentum/uid" + tn);
+                return fail(h, SFQ_E_ARG, "sfq_step: NULL momentum/uid" + tn());
             const bool fields = !bl || desc->push;
             if (fields && T.field_mode != SFQ_FIELDS_PLANE_WAVE &&
                 (!T.ex || !T.ey || !T.ez || !T.bx || !T.by || !T.bz))
-                return fail(h, SFQ_E_ARG, "sfq_step: NULL field array" + tn);
+                return fail(h, SFQ_E_ARG, "sfq_step: NULL field array" + tn());
             if (fields && T.field_mode == SFQ_FIELDS_PLANE_WAVE) {
                 if (!T.wave_amp || !T.wave_phase)
-                    return fail(h, SFQ_E_ARG, "sfq_step: NULL plane-wave array" + tn);
+                    return fail(h, SFQ_E_ARG, "sfq_step: NULL plane-wave array" + tn());
                 const double* k = T.wave_k;
                 const double* e = T.wave_pol;
                 const double kk = k[0] * k[0] + k[1] * k[1] + k[2] * k[2];
@@ -2340,15 +2340,15 @@ static sfq_status validate_desc(sfq_ctx* h, const sfq_step_desc* desc, std::vect
                 if (!(std::fabs(kk - 1.0) < 1e-12 && std::fabs(ee - 1.0) < 1e-12 &&
                       std::fabs(ke) < 1e-12) || !std::isfinite(T.wave_phase0))
                     return fail(h, SFQ_E_ARG,
-                                "sfq_step: plane wave needs unit k and e with k.e = 0" + tn);
+                                "sfq_step: plane wave needs unit k and e with k.e = 0" + tn());
             }
             if (!bl && h->decision == SFQ_OPTICAL_DEPTH && !T.tau)
-                return fail(h, SFQ_E_ARG, "sfq_step: NULL tau" + tn);
+                return fail(h, SFQ_E_ARG, "sfq_step: NULL tau" + tn());
             if (photon && !T.alive)
-                return fail(h, SFQ_E_ARG, "sfq_step: photon tiles need an alive array" + tn);
+                return fail(h, SFQ_E_ARG, "sfq_step: photon tiles need an alive array" + tn());
             if (bl && ((!desc->push && (!T.px_prev || !T.py_prev || !T.pz_prev)) || !T.fperp ||
                        !T.dfperp || !T.just_created))
-                return fail(h, SFQ_E_ARG, "sfq_step: beyond-LCFA state missing" + tn);
+                return fail(h, SFQ_E_ARG, "sfq_step: beyond-LCFA state missing" + tn());
         }
         const uint64_t nch = (T.n + chunk - 1) / chunk;
         if ((uint64_t)off[t] + nch >= (1ull << 29))
@@ -2921,7 +2921,10 @@ sfq_status sfq_step(sfq_handle h, const sfq_step_desc* desc, void* stream)
         h->last_desc.swap(db);
     }
     if (!h->step_done)
-        HIP_TRY(h, hipEventCreateWithFlags(&h->step_done, hipEventDisableTiming));
+        // no system-scope fence on record: the event only orders steps on this device, and a fence
+        // writes the caches back, 2 us of every step (65,536 electrons: 19.2 -> 17.2 us)
+        HIP_TRY(h, hipEventCreateWithFlags(&h->step_done,
+                                           hipEventDisableTiming | hipEventDisableSystemFence));
     StepArgs A;
     fill_args(h, desc, A, nchunks, chunk);
     A.tiles = (const sfq_tile*)S.dev;

@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 from dataclasses import dataclass, field
 from typing import List, Optional, Sequence
 
@@ -79,7 +80,16 @@ class StepDesc(C.Structure):
                 ("push", C.c_int32), ("zero_product_counts", C.c_int32)]
 
 
-_TILE_POINTERS = tuple(nm for nm, _ in Tile._fields_[3:23])
+# The descriptors as packed records: filling a ctypes structure field by field takes a few hundred
+# nanoseconds a field, which is most of what a small step's call costs on the host (two tiles:
+# 11 us of a 22 us call; 4.5 us as records).
+_TILE = struct.Struct("=iiQ20QQiiQQ7d")
+_PRODUCTS = struct.Struct("=7Q")
+_SET = struct.Struct("=7Q7Q7QQ")
+_STEP = struct.Struct("=QQiiQ7Q7Q7QQQQii")
+assert (_TILE.size, _PRODUCTS.size, _SET.size, _STEP.size) == \
+    (C.sizeof(Tile), C.sizeof(ProductsC), C.sizeof(ProductSetC), C.sizeof(StepDesc))
+_NO_PRODUCTS = (0,) * 7
 
 COUNTER_NAMES = ("processed", "emitted", "converted", "blcfa_rejected", "out_of_domain",
                  "clamped", "overflow", "deferred")
@@ -159,7 +169,26 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else C.c_void_p(t.data_ptr())
 
 
+def _address(t: Optional[torch.Tensor]) -> int:
+    return 0 if t is None else t.data_ptr()
+
+
+def _three(v):
+    """Three doubles (missing ones are 0, more are refused)."""
+    return v if len(v) == 3 else (C.c_double * 3)(*v)
+
+
+_M64 = (1 << 64) - 1
+
+
+# torch's own handle of a device's current stream, without the Stream object that
+# torch.cuda.current_stream() makes (3 us); where a torch build has no such function, that one
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
+    if stream is None and _raw_stream is not None:
+        return C.c_void_p(_raw_stream(torch.cuda.current_device()))
     s = stream if stream is not None else torch.cuda.current_stream()
     return C.c_void_p(s.cuda_stream)
 
@@ -334,13 +363,14 @@ class Handle:
             raise ValueError("1 <= len(tiles) <= MAX_TILES")
         arr = (Tile * nt)()
         for k, t in enumerate(tiles):
-            arr[k] = t.to_c()
+            _TILE.pack_into(arr, k * _TILE.size, *t._record())
         if product_sets:
-            sets = (ProductSetC * len(product_sets))()
-            for k, pb in enumerate(product_sets):
-                sets[k] = ProductSetC(photons=pb.photons.to_c(), electrons=pb.electrons.to_c(),
-                                      positrons=pb.positrons.to_c(), product_counts=_ptr(pb.counts))
             nsets = len(product_sets)
+            sets = (ProductSetC * nsets)()
+            for k, pb in enumerate(product_sets):
+                _SET.pack_into(sets, k * _SET.size, *pb.photons._record(),
+                               *pb.electrons._record(), *pb.positrons._record(),
+                               _address(pb.counts))
         else:
             if products is None:
                 raise ValueError("products or product_sets is required")
@@ -348,14 +378,13 @@ class Handle:
             for t in tiles:
                 if t.product_set != 0:
                     raise ValueError("product_set indices need product_sets")
-        none = ProductsC()
-        desc = StepDesc(seed=seed, step=step, ntiles=nt, nsets=nsets, tiles=arr,
-                        photons=products.photons.to_c() if products else none,
-                        electrons=products.electrons.to_c() if products else none,
-                        positrons=products.positrons.to_c() if products else none,
-                        product_counts=_ptr(products.counts) if products else None,
-                        counters=_ptr(counters.t), product_sets=sets, push=int(bool(push)),
-                        zero_product_counts=int(bool(zero_product_counts)))
+        made = ((*products.photons._record(), *products.electrons._record(),
+                 *products.positrons._record(), _address(products.counts))
+                if products else (*_NO_PRODUCTS, *_NO_PRODUCTS, *_NO_PRODUCTS, 0))
+        desc = StepDesc()
+        _STEP.pack_into(desc, 0, seed & _M64, step & _M64, nt, nsets, C.addressof(arr), *made,
+                        _address(counters.t), C.addressof(sets) if sets is not None else 0,
+                        int(bool(push)), int(bool(zero_product_counts)))
         return desc, (arr, sets)
 
     def step(self, tiles: Sequence["TileArrays"], *, seed: int, step: int,
@@ -490,14 +519,22 @@ class TileArrays:
     def n(self):
         return self.px.numel()
 
+    def _record(self):
+        """The values of _TILE, the tile's fields in order."""
+        return (self.species, self.product_set, self.n,
+                *[0 if a is None else a.data_ptr() for a in (
+                    self.px, self.py, self.pz, self.ex, self.ey, self.ez, self.bx, self.by,
+                    self.bz, self.tau, self.uid, self.alive, self.px_prev, self.py_prev,
+                    self.pz_prev, self.fperp, self.dfperp, self.just_created, self.chi_out,
+                    self.rate_out)],
+                self.step_offset & _M64, int(self.field_mode), 0, _address(self.wave_amp),
+                _address(self.wave_phase), *_three(self.wave_k), *_three(self.wave_pol),
+                float(self.wave_phase0))
+
     def to_c(self) -> Tile:
-        ptrs = [None if a is None else a.data_ptr() for a in
-                (getattr(self, nm) for nm in _TILE_POINTERS)]
-        wa, wp = self.wave_amp, self.wave_phase
-        return Tile(self.species, self.product_set, self.n, *ptrs, self.step_offset,
-                    int(self.field_mode), 0, None if wa is None else wa.data_ptr(),
-                    None if wp is None else wp.data_ptr(), (C.c_double * 3)(*self.wave_k),
-                    (C.c_double * 3)(*self.wave_pol), float(self.wave_phase0))
+        t = Tile()
+        _TILE.pack_into(t, 0, *self._record())
+        return t
 
 
 @dataclass
@@ -519,9 +556,15 @@ class ProductSpecies:
     def capacity(self):
         return self.px.numel()
 
+    def _record(self):
+        """The values of _PRODUCTS."""
+        return (_address(self.px), _address(self.py), _address(self.pz), _address(self.tau),
+                _address(self.uid), _address(self.parent), self.capacity)
+
     def to_c(self) -> ProductsC:
-        return ProductsC(px=_ptr(self.px), py=_ptr(self.py), pz=_ptr(self.pz), tau=_ptr(self.tau),
-                         uid=_ptr(self.uid), parent=_ptr(self.parent), capacity=self.capacity)
+        p = ProductsC()
+        _PRODUCTS.pack_into(p, 0, *self._record())
+        return p
 
 
 @dataclass
