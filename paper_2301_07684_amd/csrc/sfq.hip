@@ -66,7 +66,8 @@ struct StepArgs {
     int decision;
     int blcfa;
     uint32_t step;
-    const unsigned long long* step_ptr;  // if set, the step index is read from device memory
+    unsigned long long* step_ptr;  // if set, the step index is read from device memory, where
+                                   // the emitter kernel advances it
     uint64_t seed;
     // emitter queue (SoA).  Wave w of streaming block b owns the slice s = STEP_WAVES b + w,
     // entries [s cap, (s+1) cap): leptons from the start of the slice upwards, photons from its
@@ -112,9 +113,11 @@ struct StepArgs {
 
 // The control words (the first 256 bytes of the queue memory, cleared once and left cleared by
 // every step): shares deferred, next deferred share to step, deferred-share blocks done, next
-// chunk to stream; and, written by every step's streaming kernel, the product counts before the
-// step (three 64-bit words), from which the emitter blocks count their slots.
-enum { CTL_DEFERRED = 0, CTL_DEFER_NEXT = 1, CTL_DEFER_DONE = 2, CTL_CHUNK = 4, CTL_BASE = 8 };
+// chunk to stream; and, written by every step's streaming kernel, the step index of a plan and
+// the product counts before the step (three 64-bit words), from which the emitter blocks count
+// their slots.
+enum { CTL_DEFERRED = 0, CTL_DEFER_NEXT = 1, CTL_DEFER_DONE = 2, CTL_CHUNK = 4, CTL_STEP = 5,
+       CTL_BASE = 8 };
 
 enum { CNT_PROCESSED, CNT_EMITTED, CNT_CONVERTED, CNT_REJECTED, CNT_OOD, CNT_CLAMPED, CNT_OVERFLOW,
        CNT_DEFERRED, CNT_N };
@@ -1233,6 +1236,9 @@ __device__ __forceinline__ void stream_block(const StepArgs& A, int b, int G, RT
             A.zero_counts ? 0ull : A.prod_counts[tid];
         if (BLCFA && A.zero_counts && tid == 0) A.prod_counts[0] = 0;
     }
+    // product sets take their slots by atomics in the later kernels: zeroed here
+    if (A.nsets > 0 && A.zero_counts && b == 0)
+        for (int k = tid; k < 3 * A.nsets; k += STEP_BLOCK) A.sets[k / 3].product_counts[k % 3] = 0;
     __syncthreads();
 
     unsigned long long c_proc = 0, c_ood = 0;
@@ -1241,6 +1247,9 @@ __device__ __forceinline__ void stream_block(const StepArgs& A, int b, int G, RT
     QueueSink sink{slice * A.q_cap_per_wave, 0u, 0u};
     const uint32_t share = (uint32_t)(A.chunk / STEP_WAVES);  // most particles of a wave's share
     const uint32_t base_step = A.step_ptr ? (uint32_t)*A.step_ptr : A.step;
+    // the emitter kernel's block 0 advances a plan's step while the others, and the deferred-share
+    // kernel, read this copy
+    if (A.step_ptr && b == 0 && tid == 0) A.d_ctl[CTL_STEP] = base_step;
 
     // every chunk index is streamed (or deferred) by the block that got it; G blocks of at most
     // max_chunks >= ceil(N / G) each take all N
@@ -1511,6 +1520,7 @@ __device__ __forceinline__ void emit_bookkeeping(const StepArgs& A)
         A.obs[1] = A.d_ctl[CTL_DEFERRED];
     }
     A.d_ctl[CTL_CHUNK] = 0;  // the next step's streaming kernel takes chunks from 0 again
+    if (A.step_ptr) *A.step_ptr += 1;
 }
 
 template <bool MIXED, bool BLCFA, bool LOCAL>
@@ -1524,7 +1534,7 @@ __global__ __launch_bounds__(STEP_BLOCK, SFQ_EMIT_WAVES) void emit_kernel(StepAr
         emit_bookkeeping<BLCFA>(A);
         return;
     }
-    const uint32_t base_step = A.step_ptr ? (uint32_t)*A.step_ptr : A.step;
+    const uint32_t base_step = A.step_ptr ? A.d_ctl[CTL_STEP] : A.step;
     unsigned long long base[3] = {0, 0, 0};
     if (A.nsets == 0) {
         const unsigned long long* b =
@@ -1602,7 +1612,7 @@ __global__ __launch_bounds__(STEP_BLOCK, 1) void defer_kernel(StepArgs A)
     const int tid = threadIdx.x;
     if (tid < CNT_N) s_cnt[tid] = 0;
     __syncthreads();
-    const uint32_t base_step = A.step_ptr ? (uint32_t)*A.step_ptr : A.step;
+    const uint32_t base_step = A.step_ptr ? A.d_ctl[CTL_STEP] : A.step;
     const RT* g_rad = MIXED ? (const RT*)A.tb.rad32 : (const RT*)A.tb.rad;
     const RT* g_pair = MIXED ? (const RT*)A.tb.pair32 : (const RT*)A.tb.pair;
     EmitCounts C;
@@ -1634,17 +1644,16 @@ __global__ __launch_bounds__(STEP_BLOCK, 1) void defer_kernel(StepArgs A)
     }
 }
 
-// step helpers: zero the product counts of product sets (a kernel, not a memset, so graphs
-// replay it safely) and advance a plan's device step counter after a step
-__global__ void zero_set_counts_kernel(const sfq_product_set* sets, int nsets)
+// The descriptors of a step, from the pinned host buffer they were gathered in to their device
+// copy, and, for scratch that starts undefined, the control words cleared: one launch, where a
+// copy command (4 us and a gap of 10 after the event before it) and a clear were two commands.
+__global__ __launch_bounds__(256) void upload_kernel(const uint4* host, uint4* dev, size_t n16,
+                                                     unsigned* ctl)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < 3 * nsets) sets[k / 3].product_counts[k % 3] = 0;
-}
-
-__global__ void advance_step_kernel(unsigned long long* step)
-{
-    if (threadIdx.x == 0) *step += 1;
+    const size_t step = (size_t)gridDim.x * blockDim.x;
+    for (size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x; k < n16; k += step)
+        dev[k] = host[k];
+    if (ctl && blockIdx.x == 0 && threadIdx.x < 64) ctl[threadIdx.x] = 0;
 }
 
 __global__ void set_step_kernel(unsigned long long* step, unsigned long long value)
@@ -1766,6 +1775,7 @@ thread_local std::string tl_error = "";
 
 struct Staging {
     void* host = nullptr;   // pinned
+    void* mapped = nullptr; // its device address
     void* dev = nullptr;
     hipEvent_t done = nullptr;
     size_t bytes = 0;
@@ -1841,6 +1851,7 @@ struct sfq_ctx {
     // uploading the descriptors (all set up by sfq_create; null when that failed)
     void* na_scratch = nullptr;
     void* na_host = nullptr;
+    void* na_mapped = nullptr;     // its device address
     hipEvent_t na_done = nullptr;
 };
 
@@ -2071,9 +2082,14 @@ sfq_status sfq_create(const sfq_config* cfg, sfq_handle* out)
         h->na_scratch = g_scratch_ptr[h->device];
     }
     if (h->na_scratch) {
-        if (hipHostMalloc(&h->na_host, STAGING_BYTES, hipHostMallocDefault) != hipSuccess)
+        if (hipHostMalloc(&h->na_host, STAGING_BYTES, hipHostMallocMapped) != hipSuccess)
             h->na_host = nullptr;
-        if (hipEventCreateWithFlags(&h->na_done, hipEventDisableTiming) != hipSuccess)
+        if (h->na_host && hipHostGetDevicePointer(&h->na_mapped, h->na_host, 0) != hipSuccess) {
+            (void)hipHostFree(h->na_host);
+            h->na_host = h->na_mapped = nullptr;
+        }
+        if (hipEventCreateWithFlags(&h->na_done,
+                                    hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess)
             h->na_done = nullptr;
     }
     (void)hipGetLastError();
@@ -2637,20 +2653,19 @@ static void plan_release(sfq_plan_t* p)
     delete p;
 }
 
-// Zeroes the product counts of a step with product sets (a kernel, not a memset, so graphs
-// replay it safely).  Steps without sets need none: their emitter kernel starts from zero.
-static void enqueue_zero_counts(const StepArgs& A, hipStream_t st)
-{
-    if (A.nsets > 0)
-        hipLaunchKernelGGL(zero_set_counts_kernel, dim3((3 * A.nsets + 255) / 256), dim3(256), 0, st,
-                           A.sets, A.nsets);
-}
-
 static void plan_enqueue(sfq_plan_t* p, hipStream_t st, const ProfEvents* pe = nullptr)
 {
-    if (p->zero_counts) enqueue_zero_counts(p->A, st);
     launch_step_kernels(p->h, p->A, p->grid, st, pe);
-    hipLaunchKernelGGL(advance_step_kernel, dim3(1), dim3(64), 0, st, p->d_step);
+}
+
+// Enqueues the copy of `used` bytes of descriptors from `mapped` (the device address of a pinned
+// host buffer of a multiple of 16 bytes) to `dev`, and the clearing of `ctl` if it is given.
+static void upload(const void* mapped, void* dev, size_t used, unsigned* ctl, hipStream_t st)
+{
+    const size_t n16 = (used + 15) / 16;
+    const int blocks = (int)std::min<size_t>(256, (n16 + 255) / 256);
+    hipLaunchKernelGGL(upload_kernel, dim3(blocks), dim3(256), 0, st, (const uint4*)mapped,
+                       (uint4*)dev, n16, ctl);
 }
 
 static QueueShape queue_capacity(const sfq_ctx* h)
@@ -2906,17 +2921,20 @@ sfq_status sfq_step(sfq_handle h, const sfq_step_desc* desc, void* stream)
             HIP_TRY(h, hipEventRecord(h->staging[h->last_slot].done, (hipStream_t)stream));
         const int slot = h->next_staging;
         h->next_staging = (h->next_staging + 1) % N_STAGING;
-        if (!S.host) {
-            HIP_TRY(h, hipHostMalloc(&S.host, STAGING_BYTES, hipHostMallocDefault));
-            HIP_TRY(h, hipMalloc(&S.dev, STAGING_BYTES));
-            HIP_TRY(h, hipEventCreateWithFlags(&S.done, hipEventDisableTiming));
+        if (!S.done) {
+            if (!S.host) HIP_TRY(h, hipHostMalloc(&S.host, STAGING_BYTES, hipHostMallocMapped));
+            HIP_TRY(h, hipHostGetDevicePointer(&S.mapped, S.host, 0));
+            if (!S.dev) HIP_TRY(h, hipMalloc(&S.dev, STAGING_BYTES));
+            // fence-free: the host only needs to know that the slot was read
+            HIP_TRY(h, hipEventCreateWithFlags(&S.done,
+                                               hipEventDisableTiming | hipEventDisableSystemFence));
             S.bytes = STAGING_BYTES;
         } else {
             HIP_TRY(h, hipEventSynchronize(S.done));
         }
         memcpy(S.host, db.data(), used);
-        HIP_TRY(h, hipMemcpyAsync(S.dev, S.host, used, hipMemcpyHostToDevice,
-                                  (hipStream_t)stream));
+        upload(S.mapped, S.dev, used, nullptr, (hipStream_t)stream);
+        HIP_TRY(h, hipGetLastError());
         h->last_slot = slot;
         h->last_desc.swap(db);
     }
@@ -2932,7 +2950,6 @@ sfq_status sfq_step(sfq_handle h, const sfq_step_desc* desc, void* stream)
     if (desc->nsets > 0) A.sets = (const sfq_product_set*)((char*)S.dev + set_pos);
     bind_queue(h, A, h->d_queue, queue_capacity(h), qs);
     A.obs = h->obs_dev;
-    if (desc->zero_product_counts) enqueue_zero_counts(A, (hipStream_t)stream);
     const ProfEvents* pe = prof_events(h);
     launch_step_kernels(h, A, qs.grid, (hipStream_t)stream, pe);
     HIP_TRY(h, hipGetLastError());
@@ -3033,17 +3050,16 @@ sfq_status sfq_step_noalloc(sfq_handle h, const sfq_step_desc* desc, void* strea
     if (desc->nsets > 0)
         memcpy(hb + set_pos, desc->product_sets, desc->nsets * sizeof(sfq_product_set));
     char* sc = (char*)h->na_scratch;  // the device address, never the array's name
-    HIP_TRY(h, hipMemcpyAsync(sc, hb, used, hipMemcpyHostToDevice, (hipStream_t)stream));
     // the deferral words must start at zero: the deferred-share kernel's last block leaves them
     // so, but the array holds whatever the last call on this device left
-    HIP_TRY(h, hipMemsetAsync(sc + STAGING_BYTES, 0, 256, (hipStream_t)stream));
+    upload(h->na_mapped, sc, used, (unsigned*)(sc + STAGING_BYTES), (hipStream_t)stream);
+    HIP_TRY(h, hipGetLastError());
     StepArgs A;
     fill_args(h, desc, A, nchunks, chunk);
     A.tiles = (const sfq_tile*)sc;
     A.chunk_off = (const uint32_t*)(sc + off_pos);
     if (desc->nsets > 0) A.sets = (const sfq_product_set*)(sc + set_pos);
     bind_queue(h, A, sc + STAGING_BYTES, qs, qs);
-    if (desc->zero_product_counts) enqueue_zero_counts(A, (hipStream_t)stream);
     launch_step_kernels(h, A, qs.grid, (hipStream_t)stream, nullptr);
     HIP_TRY(h, hipGetLastError());
     HIP_TRY(h, hipEventRecord(h->na_done, (hipStream_t)stream));
