@@ -93,3 +93,41 @@ def test_reserved_steps_allocate_nothing():
                    counters=sfq.Counters(dev), push=True)
             assert h.queue_bytes() == held, (n, form)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2, 7, 8, 15, 16, 17])
+@pytest.mark.parametrize("n", [1, 15, 256, 257, 12293, 65521])
+@pytest.mark.parametrize("shape", [(1, 256), (8, 1024), None])
+def test_slices_step_as_their_copies(offset, n, shape):
+    """Tiles that start anywhere in larger arrays (their chunks are cut at 128-byte lines) give the
+    bits their aligned copies give, and touch nothing beside the slice."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dev = torch.device("cuda", 0)
+    h = sfq.Handle(ref_length=inputs.LAMBDA_R, dt=inputs.DT)
+    if shape:
+        h.set_launch(*shape)
+    whole = tiles(dev, h, n + 40, "arrays", False)
+    got = []
+    for copy in (False, True):
+        pb, cnt, ts, kept = sfq.ProductBuffers.empty(n + 40, n + 40, dev), sfq.Counters(dev), [], []
+        for t in whole:
+            if t.n <= offset:
+                continue
+            m = min(n, t.n - offset)
+            full = {f: getattr(t, f).clone() for f in (
+                "px", "py", "pz", "ex", "ey", "ez", "bx", "by", "bz", "tau", "uid", "alive")}
+            kept.append((full, {f: v.clone() for f, v in full.items()}, m))
+            part = {f: v[offset:offset + m].clone() if copy else v[offset:offset + m]
+                    for f, v in full.items()}
+            ts.append(sfq.TileArrays(t.species, **part))
+        if not ts:
+            return
+        h.step(ts, seed=5, step=2, products=pb, counters=cnt, push=True, zero_product_counts=True)
+        got.append((result(ts, pb), cnt.results()))
+        for full, before, m in kept:
+            for f in full:
+                assert torch.equal(full[f][:offset], before[f][:offset])
+                assert torch.equal(full[f][offset + m:], before[f][offset + m:])
+    (a, ca), (b, cb) = got
+    assert ca == cb and all(torch.equal(x, y) for x, y in zip(a, b))
