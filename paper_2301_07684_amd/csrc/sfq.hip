@@ -1967,7 +1967,9 @@ static sfq_status load_tables(sfq_ctx* h, const char* path_in)
     const size_t sizes[6] = {RAD_SIZE, PAIR_SIZE, KA_SIZE, KB_SIZE, PHINV_SIZE, PPINV_SIZE};
     size_t total = 0;
     for (size_t s : sizes) total += s;
-    std::vector<double> host64(total);
+    // the rate segments again, in padded rows, behind the arrays of the file
+    const size_t even = (total + 3) & ~(size_t)3;
+    std::vector<double> host64(even + RAD_ROWS<double> + PAIR_ROWS<double>);
     size_t o = 0;
     for (int a = 0; a < 6; ++a) {
         uint64_t cnt;
@@ -1980,12 +1982,8 @@ static sfq_status load_tables(sfq_ctx* h, const char* path_in)
         pos += cnt * 8;
         o += cnt;
     }
-    std::vector<float> host32(total);
+    std::vector<float> host32(even + RAD_ROWS<float> + PAIR_ROWS<float>);
     for (size_t k = 0; k < total; ++k) host32[k] = (float)host64[k];
-    // the rate segments again, in padded rows, behind the arrays of the file
-    const size_t even = (total + 3) & ~(size_t)3;
-    host64.resize(even + RAD_ROWS<double> + PAIR_ROWS<double>);
-    host32.resize(even + RAD_ROWS<float> + PAIR_ROWS<float>);
     for (int seg = 0; seg < N_CHI_SEG + N_PAIR_SEG; ++seg)
         for (int k = 0; k < RATE_DEG; ++k) {
             const double c = host64[(size_t)seg * RATE_DEG + k];  // rad, then pair
