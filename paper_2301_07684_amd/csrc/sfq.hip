@@ -4,12 +4,12 @@
 // equation behind every device function.
 //
 // Kernel design (gfx950, wave64):
-//   bulk_kernel  persistent streaming pass over all tiles of a step: coalesced FP64 SoA loads
+//   bulk_kernel  streaming pass over all tiles of a step: coalesced FP64 SoA loads
 //                in one group per iteration, the fields (arrays, one uniform value, or a plane
 //                wave computed here), the optional Boris push, gamma, chi, the rate from
 //                LDS-staged coefficient tables and the decision (or the beyond-LCFA force
 //                update); emitters are compacted with a wave ballot + popcount prefix into the
-//                block's own slice of a queue (one LDS atomic per wave, no global atomics).  It
+//                wave's own slice of a queue (counts in scalar registers, no atomics).  It
 //                writes every slot of a chunk it updates (whole cache lines), addresses each
 //                chunk from its first element (scalar bases, one 32-bit lane offset), and
 //                carries none of the sampling code, so its register footprint stays small.
@@ -336,13 +336,15 @@ constexpr int STEP_BLOCK = 256;
 // (which leave the emission threshold's transcendentals to the emitter pass) fit 5 waves
 // (mixed), 4 (mixed with the push, FP64) or 3 (FP64 with the push).  The kernels that take
 // plane-wave tiles (fields computed in the kernel, two particles per lane in the LCFA loop)
-// get 4 waves (LCFA) or 3 (beyond-LCFA).
+// get 4 waves (LCFA; beyond-LCFA mixed, where the loop waits on arithmetic as much as on memory:
+// 2 registers spilled outside it, a served batch of 3 million particles 105 us against 109 at 3
+// waves, 1.8 million 67 against 71) or 3 (beyond-LCFA FP64, which needs 147 registers).
 #ifdef SFQ_BULK_WAVES
 constexpr int bulk_waves(bool, bool, bool, bool) { return SFQ_BULK_WAVES; }
 #else
 constexpr int bulk_waves(bool mixed, bool blcfa, bool push, bool wave)
 {
-    if (blcfa) return wave ? 3 : (mixed ? (push ? 4 : 5) : (push ? 3 : 4));
+    if (blcfa) return wave ? (mixed ? 4 : 3) : (mixed ? (push ? 4 : 5) : (push ? 3 : 4));
     return wave ? 4 : (mixed ? 5 : 4);
 }
 #endif
