@@ -332,19 +332,20 @@ constexpr int STEP_BLOCK = 256;
 // streaming kernel's register budget decides how many waves can hide HBM latency: the LCFA
 // array forms, with their two-particles-per-lane loop, fit 4 waves (FP64) and 5 (mixed); the
 // launch shapes that run best use 2 per SIMD (2 blocks of 4 waves per compute unit), with two
-// independent particles per lane.  The beyond-LCFA forms
-// (which leave the emission threshold's transcendentals to the emitter pass) fit 5 waves
-// (mixed), 4 (mixed with the push, FP64) or 3 (FP64 with the push).  The kernels that take
-// plane-wave tiles (fields computed in the kernel, two particles per lane in the LCFA loop)
-// get 4 waves (LCFA; beyond-LCFA mixed, where the loop waits on arithmetic as much as on memory:
-// 2 registers spilled outside it, a served batch of 3 million particles 105 us against 109 at 3
-// waves, 1.8 million 67 against 71) or 3 (beyond-LCFA FP64, which needs 147 registers).
+// independent particles per lane.  The beyond-LCFA forms (which leave the emission threshold's
+// transcendentals to the emitter pass) wait on arithmetic as much as on memory, and gain from a
+// fourth wave where its 128 registers hold them: array tiles (5 waves mixed without the push; FP64
+// with the push, 130 registers and 3 waves uncapped, 1.6 million particles 60 us against 66,
+// 1.2e7 370 against 392, 1.8e7 526 against 568, 3.2e7 938 against 1029; 1e7 318 against 313) and
+// mixed plane-wave tiles (2 registers spilled outside the loop, 3 million 105 against 109, 3.2e7
+// 930 against 1033).  FP64 plane-wave tiles need 147 registers: 3 waves.  The other kernels that
+// take plane-wave tiles (fields computed in the kernel, two particles per lane) get 4.
 #ifdef SFQ_BULK_WAVES
 constexpr int bulk_waves(bool, bool, bool, bool) { return SFQ_BULK_WAVES; }
 #else
 constexpr int bulk_waves(bool mixed, bool blcfa, bool push, bool wave)
 {
-    if (blcfa) return wave ? (mixed ? 4 : 3) : (mixed ? (push ? 4 : 5) : (push ? 3 : 4));
+    if (blcfa) return wave ? (mixed ? 4 : 3) : (mixed && !push ? 5 : 4);
     return wave ? 4 : (mixed ? 5 : 4);
 }
 #endif
