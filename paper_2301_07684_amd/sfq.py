@@ -90,6 +90,7 @@ _STEP = struct.Struct("=QQiiQ7Q7Q7QQQQii")
 assert (_TILE.size, _PRODUCTS.size, _SET.size, _STEP.size) == \
     (C.sizeof(Tile), C.sizeof(ProductsC), C.sizeof(ProductSetC), C.sizeof(StepDesc))
 _NO_PRODUCTS = (0,) * 7
+_vec3 = C.c_double * 3
 
 COUNTER_NAMES = ("processed", "emitted", "converted", "blcfa_rejected", "out_of_domain",
                  "clamped", "overflow", "deferred")
@@ -175,10 +176,18 @@ def _address(t: Optional[torch.Tensor]) -> int:
 
 def _three(v):
     """Three doubles (missing ones are 0, more are refused)."""
-    return v if len(v) == 3 else (C.c_double * 3)(*v)
+    return v if type(v) is tuple and len(v) == 3 else _vec3(*v)
 
 
-_M64 = (1 << 64) - 1
+def _pack_tile(tile, buffer, offset):
+    """The tile's record at `offset` of `buffer`, holding what the fields of Tile take: values that the
+    packed form refuses (whole numbers wider than a field, which are cut to it) go through those."""
+    record = tile._record()
+    try:
+        _TILE.pack_into(buffer, offset, *record)
+    except struct.error:
+        t = Tile(*record[:28], _vec3(*record[28:31]), _vec3(*record[31:34]), record[34])
+        C.memmove(C.addressof(buffer) + offset, C.addressof(t), _TILE.size)
 
 
 # torch's own handle of a device's current stream, without the Stream object that
@@ -363,7 +372,7 @@ class Handle:
             raise ValueError("1 <= len(tiles) <= MAX_TILES")
         arr = (Tile * nt)()
         for k, t in enumerate(tiles):
-            _TILE.pack_into(arr, k * _TILE.size, *t._record())
+            _pack_tile(t, arr, k * _TILE.size)
         if product_sets:
             nsets = len(product_sets)
             sets = (ProductSetC * nsets)()
@@ -382,9 +391,10 @@ class Handle:
                  *products.positrons._record(), _address(products.counts))
                 if products else (*_NO_PRODUCTS, *_NO_PRODUCTS, *_NO_PRODUCTS, 0))
         desc = StepDesc()
-        _STEP.pack_into(desc, 0, seed & _M64, step & _M64, nt, nsets, C.addressof(arr), *made,
+        _STEP.pack_into(desc, 0, 0, 0, nt, nsets, C.addressof(arr), *made,
                         _address(counters.t), C.addressof(sets) if sets is not None else 0,
                         int(bool(push)), int(bool(zero_product_counts)))
+        desc.seed, desc.step = seed, step  # any integer type, modulo 2^64
         return desc, (arr, sets)
 
     def step(self, tiles: Sequence["TileArrays"], *, seed: int, step: int,
@@ -527,13 +537,13 @@ class TileArrays:
                     self.bz, self.tau, self.uid, self.alive, self.px_prev, self.py_prev,
                     self.pz_prev, self.fperp, self.dfperp, self.just_created, self.chi_out,
                     self.rate_out)],
-                self.step_offset & _M64, int(self.field_mode), 0, _address(self.wave_amp),
+                self.step_offset, int(self.field_mode), 0, _address(self.wave_amp),
                 _address(self.wave_phase), *_three(self.wave_k), *_three(self.wave_pol),
                 float(self.wave_phase0))
 
     def to_c(self) -> Tile:
         t = Tile()
-        _TILE.pack_into(t, 0, *self._record())
+        _pack_tile(self, t, 0)
         return t
 
 
