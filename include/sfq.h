@@ -340,10 +340,14 @@ sfq_status sfq_plan_replay(sfq_plan p, void* stream);
  * particles of such shares).  Streaming blocks take chunks as they become free, up to their
  * even share plus a sixteenth; a slice holds one share plus `2 * expected_fraction` of the
  * particles of that many shares (at most all of them, which makes deferral impossible).
+ * Where no launch shape is set, steps of up to about 8.4 million particles give every block one
+ * chunk, and the queue then has an entry for every slot of the chunks, whatever the fraction: at
+ * most one per particle and 2^20 more (48 to 72 bytes each; steps whose tiles would need more,
+ * because they end far inside their chunks, run on fewer blocks, with a queue by the fraction).
  *
  * Pre-sizes the queue for sfq_step calls of up to `max_particles` particles in up to
- * `max_tiles` tiles with the current launch shape and queue fraction, so that such calls
- * allocate nothing.  A larger step, one after a change of launch shape, or one after the queue
+ * `max_tiles` tiles with the launch shape that is set, or any that such calls pick where none is,
+ * and the current queue fraction, so that such calls allocate nothing.  A larger step, one after a change of launch shape, or one after the queue
  * fraction grew still grows the queue, which waits for the device.  SFQ_E_NOMEM if the
  * allocation fails. */
 sfq_status sfq_reserve(sfq_handle h, uint64_t max_particles, int max_tiles);

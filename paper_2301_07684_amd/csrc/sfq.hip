@@ -2312,36 +2312,61 @@ static LaunchShape set_shape(const sfq_ctx* h)
     return {h->num_cus * h->blocks_per_cu, h->chunk};
 }
 
+// A tile's chunks (its first one is short by line_shift).
+static uint64_t tile_chunks(const sfq_tile& T, int chunk)
+{
+    return T.n ? (T.n + line_shift(T.px) + chunk - 1) / chunk : 0;
+}
+
 // The shape of a step of n particles when none is set (times of the streaming kernel on 256
 // compute units).
-//   Up to 8 blocks per compute unit (16 beyond LCFA) of the largest chunk, about 8.4 million
-//   particles: every block streams one chunk, with no counter to ask for a next one, and the
-//   hardware hands out the blocks.  The chunk makes about two blocks per compute unit (twelve
+//   One chunk per block, up to 8 blocks per compute unit (16 beyond LCFA) of the largest chunk, about
+//   8.4 million particles: there is no counter to ask for a next chunk, and the hardware hands out
+//   the blocks.  The chunk makes about two blocks per compute unit (twelve
 //   beyond LCFA, whose loop waits longest per particle): shorter ones leave each block's start
 //   (rate tables, descriptors) unpaid, longer ones leave compute units idle.  65,536 particles:
 //   chunks of 256 10 us, of 2048 15; 500,000: 1024 14, 512 15.4, 2048 17.7; 2 million: 4096 37,
 //   2048 40.5; 6 million: 4096 102, 2 x 2048 107, 8 x 2048 114; beyond LCFA 3 million: 1024 107,
 //   2048 115, 4096 129.
-//   Above, resident blocks take chunks in turn: two per compute unit where a lane streams two
+//   Resident blocks that take chunks in turn above that: two per compute unit where a lane streams two
 //   adjacent particles (2^25: 2 x 2048 521-525, 3 x 2048 537-543, 4 x 2048 558, 64 x 2048 551),
 //   three in the one-particle loops (local decisions 550, 2 x 2048 603; uniform fields, 2^26, 3 x
 //   4096 861, 2 x 4096 1013, 4 x 4096 888), four for plane-wave tiles, which compute most (2^24:
 //   4 x 4096 232, 3 x 4096 241, 2 x 4096 262) and beyond LCFA (2.3e7: 4 x 2048 718, 3 x 2048 739).
-static LaunchShape auto_shape(const sfq_ctx* h, double n, bool wave, bool uniform)
+static double one_chunk_most(const sfq_ctx* h)
+{
+    return h->blcfa ? 16.0 * h->num_cus * 2048 : 8.0 * h->num_cus * 4096;
+}
+
+static LaunchShape one_chunk_shape(const sfq_ctx* h, double n)
 {
     const bool bl = h->blcfa != 0;
-    const int cus = h->num_cus, largest = bl ? 2048 : 4096;
-    if (n <= (double)(bl ? 16 : 8) * cus * largest) {
-        const double even = n / ((bl ? 12.0 : 2.0) * cus);
-        const int unit = even > 512.0 ? 512 : 256;  // two particles per lane: 512 an iteration
-        const int chunk = unit * std::max(1, (int)std::ceil(even / unit));
-        return {1 << 29, std::min(chunk, largest)};
-    }
-    if (bl) return {4 * cus, 2048};
-    if (wave) return {4 * cus, 4096};
-    if (uniform) return {3 * cus, 4096};
+    const double even = n / ((bl ? 12.0 : 2.0) * h->num_cus);
+    const int unit = even > 512.0 ? 512 : 256;  // two particles per lane: 512 an iteration
+    const int chunk = unit * std::max(1, (int)std::ceil(even / unit));
+    return {1 << 29, std::min(chunk, bl ? 2048 : 4096)};
+}
+
+static LaunchShape resident_shape(const sfq_ctx* h, double n, bool wave, bool uniform)
+{
+    const int cus = h->num_cus;
+    // fewer particles than this come here for their short tiles, which fill chunks of 4096 badly
+    const int chunk = n > one_chunk_most(h) ? 4096 : 2048;
+    if (h->blcfa) return {4 * cus, 2048};
+    if (wave) return {4 * cus, chunk};
+    if (uniform) return {3 * cus, chunk};
     return {(h->decision == SFQ_LOCAL ? 3 : 2) * cus, 2048};
 }
+
+// One chunk per block needs a queue entry for every slot of its chunks (a block takes a chunk only
+// if all of it may emit).  Many tiles that end far inside a chunk would hold several times their
+// particles: beyond this many entries (50 to 75 MB) more than one per particle, the step runs on
+// resident blocks, whose queue follows the expected emitters.  Those are no slower there, since
+// thousands of blocks with little each also lengthen the emitter pass: 4096 tiles of 1000 particles
+// 131 us with a chunk each (806 MB), 126 resident (107 MB); 4096 of 500 96 and 92; one of 4 million
+// and 4095 of 100 151 (998 MB) and 152 (132 MB); 1000 tiles of 100 to 50,000 212 and 197 (beyond LCFA
+// 536, 688 MB, and 551, 271 MB).
+constexpr uint64_t QUEUE_SLACK = 1ull << 20;
 
 static LaunchShape launch_shape(const sfq_ctx* h, const sfq_step_desc* desc)
 {
@@ -2353,7 +2378,13 @@ static LaunchShape launch_shape(const sfq_ctx* h, const sfq_step_desc* desc)
         wave |= desc->tiles[t].field_mode == SFQ_FIELDS_PLANE_WAVE;
         uniform |= desc->tiles[t].field_mode == SFQ_FIELDS_UNIFORM;
     }
-    return auto_shape(h, n, wave, uniform);
+    if (n <= one_chunk_most(h)) {
+        const LaunchShape one = one_chunk_shape(h, n);
+        uint64_t nch = 0;
+        for (int t = 0; t < desc->ntiles; ++t) nch += tile_chunks(desc->tiles[t], one.chunk);
+        if (nch * (uint64_t)one.chunk <= (uint64_t)n + QUEUE_SLACK) return one;
+    }
+    return resident_shape(h, n, wave, uniform);
 }
 
 // Checks the descriptor and fills the tiles' chunk offsets for the launch shape `ls`, or, if that
@@ -2421,7 +2452,7 @@ static sfq_status validate_desc(sfq_ctx* h, const sfq_step_desc* desc, std::vect
                        !T.dfperp || !T.just_created))
                 return fail(h, SFQ_E_ARG, "sfq_step: beyond-LCFA state missing" + tn());
         }
-        const uint64_t nch = T.n ? (T.n + line_shift(T.px) + chunk - 1) / chunk : 0;
+        const uint64_t nch = tile_chunks(T, chunk);
         if ((uint64_t)off[t] + nch >= (1ull << 29))
             return fail(h, SFQ_E_CAPACITY, "sfq_step: too many particles in one step (at most "
                                            "2^29 - 1 chunks)");
@@ -2793,27 +2824,37 @@ sfq_status sfq_reserve(sfq_handle h, uint64_t max_particles, int max_tiles)
     if (max_tiles < 1 || max_tiles > SFQ_MAX_TILES)
         return fail(h, SFQ_E_ARG, "sfq_reserve: max_tiles in [1, SFQ_MAX_TILES]");
     std::lock_guard<std::mutex> lock(h->mu);
-    // every shape a step within the limits may take: the set one, or those that auto_shape picks
-    // by size (where it changes the chunk or the number of blocks) and form
+    // every shape a step within the limits may take, with the most chunks it can have there (a tile's
+    // first and last chunks may be short)
     std::vector<std::pair<uint64_t, LaunchShape>> shapes;
+    const uint64_t T = (uint64_t)max_tiles;
+    const auto chunks = [T](uint64_t n, int chunk) { return n / chunk + 2 * T; };
     if (!h->auto_launch) {
-        shapes.push_back({max_particles, set_shape(h)});
+        const LaunchShape s = set_shape(h);
+        shapes.push_back({chunks(max_particles, s.chunk), s});
     } else {
-        std::vector<uint64_t> sizes{max_particles};
-        const uint64_t cus = (uint64_t)h->num_cus, per = (h->blcfa ? 12 : 2) * cus;
-        for (uint64_t c = 256; c <= 4096; c += 256) sizes.push_back(per * c);
-        sizes.push_back((h->blcfa ? 16 * 2048 : 8 * 4096) * cus);
-        for (uint64_t n : sizes)
-            if (n <= max_particles)
-                for (int form = 0; form < 3; ++form)
-                    shapes.push_back({n, auto_shape(h, (double)n, form == 1, form == 2)});
+        // one chunk per block: the most particles of every chunk length within the limits
+        const uint64_t most = std::min(max_particles, (uint64_t)one_chunk_most(h));
+        bool more = false;  // may have more entries than that: resident blocks
+        for (uint64_t n = 0, c = 256; n < most; c += 256) {
+            n = std::min(most, (h->blcfa ? 12 : 2) * (uint64_t)h->num_cus * c);
+            const LaunchShape s = one_chunk_shape(h, (double)n);
+            const uint64_t nch = chunks(n, s.chunk), fit = (n + QUEUE_SLACK) / s.chunk;
+            more |= nch > fit;
+            shapes.push_back({std::min(nch, fit), s});
+        }
+        for (int form = 0; form < 3; ++form)
+            for (const uint64_t n : {most, max_particles})
+                if (n > most || more) {
+                    const LaunchShape s = resident_shape(h, (double)n, form == 1, form == 2);
+                    shapes.push_back({chunks(n, s.chunk), s});
+                }
     }
     QueueShape most{};
     for (const auto& s : shapes) {
-        // a tile's first and last chunks may be short
-        const uint64_t nch = s.first / s.second.chunk + 2 * (uint64_t)max_tiles;
-        if (nch >= (1ull << 29)) return fail(h, SFQ_E_CAPACITY, "sfq_reserve: too many particles");
-        const QueueShape q = queue_shape((int)nch, s.second, h->q_frac);
+        if (s.first >= (1ull << 29))
+            return fail(h, SFQ_E_CAPACITY, "sfq_reserve: too many particles");
+        const QueueShape q = queue_shape((int)s.first, s.second, h->q_frac);
         most.grid = std::max(most.grid, q.grid);
         most.slices = std::max(most.slices, q.slices);
         most.entries = std::max(most.entries, q.entries);
