@@ -344,6 +344,8 @@ sfq_status sfq_plan_replay(sfq_plan p, void* stream);
  * chunk, and the queue then has an entry for every slot of the chunks, whatever the fraction: at
  * most one per particle and 2^20 more (48 to 72 bytes each; steps whose tiles would need more,
  * because they end far inside their chunks, run on fewer blocks, with a queue by the fraction).
+ * A step, plan or reservation whose queue the device's memory does not hold takes the shape
+ * 8 x 2048 instead if its queue is smaller (a step or reservation for the handle's later steps too).
  *
  * Pre-sizes the queue for sfq_step calls of up to `max_particles` particles in up to
  * `max_tiles` tiles with the launch shape that is set, or any that such calls pick where none is,

@@ -2786,6 +2786,7 @@ static sfq_status ensure_queue(sfq_ctx* h, const QueueShape& qs, const char* who
         h->q_cap_grid = h->q_cap_slices = h->q_cap_entries = h->q_cap_deferrable = 0;
     }
     if (hipMalloc(&h->d_queue, queue_bytes(h, want)) != hipSuccess) {
+        (void)hipGetLastError();  // or the next launch that looks for an error finds this one
         h->d_queue = nullptr;
         return fail(h, SFQ_E_NOMEM, std::string(who) + ": cannot allocate the emitter queue");
     }
@@ -2816,14 +2817,26 @@ static void adapt_queue(sfq_ctx* h)
     o[1] = 0;
 }
 
-extern "C" {
-
-sfq_status sfq_reserve(sfq_handle h, uint64_t max_particles, int max_tiles)
+// Where the queue of a picked shape was refused: the set shape (8 x 2048 as long as none is set) with
+// its chunk offsets and queue, if that is smaller.
+static bool smaller_shape(sfq_ctx* h, const sfq_step_desc* desc, std::vector<uint32_t>& off,
+                          LaunchShape& ls, QueueShape& qs)
 {
-    if (!h) return fail(h, SFQ_E_STATE, "sfq_reserve: NULL handle");
-    if (max_tiles < 1 || max_tiles > SFQ_MAX_TILES)
-        return fail(h, SFQ_E_ARG, "sfq_reserve: max_tiles in [1, SFQ_MAX_TILES]");
-    std::lock_guard<std::mutex> lock(h->mu);
+    if (!h->auto_launch) return false;
+    LaunchShape set = set_shape(h);
+    std::vector<uint32_t> set_off;
+    if (validate_desc(h, desc, set_off, set) != SFQ_OK) return false;
+    const QueueShape q = queue_shape((int)set_off[desc->ntiles], set, h->q_frac);
+    if (queue_bytes(h, q) >= queue_bytes(h, qs)) return false;
+    off.swap(set_off);
+    ls = set;
+    qs = q;
+    return true;
+}
+
+// The queue that holds every step of up to max_particles particles in up to max_tiles tiles.
+static sfq_status reserve_shape(sfq_ctx* h, uint64_t max_particles, int max_tiles, QueueShape& most)
+{
     // every shape a step within the limits may take, with the most chunks it can have there (a tile's
     // first and last chunks may be short)
     std::vector<std::pair<uint64_t, LaunchShape>> shapes;
@@ -2834,23 +2847,23 @@ sfq_status sfq_reserve(sfq_handle h, uint64_t max_particles, int max_tiles)
         shapes.push_back({chunks(max_particles, s.chunk), s});
     } else {
         // one chunk per block: the most particles of every chunk length within the limits
-        const uint64_t most = std::min(max_particles, (uint64_t)one_chunk_most(h));
+        const uint64_t single = std::min(max_particles, (uint64_t)one_chunk_most(h));
         bool more = false;  // may have more entries than that: resident blocks
-        for (uint64_t n = 0, c = 256; n < most; c += 256) {
-            n = std::min(most, (h->blcfa ? 12 : 2) * (uint64_t)h->num_cus * c);
+        for (uint64_t n = 0, c = 256; n < single; c += 256) {
+            n = std::min(single, (h->blcfa ? 12 : 2) * (uint64_t)h->num_cus * c);
             const LaunchShape s = one_chunk_shape(h, (double)n);
             const uint64_t nch = chunks(n, s.chunk), fit = (n + QUEUE_SLACK) / s.chunk;
             more |= nch > fit;
             shapes.push_back({std::min(nch, fit), s});
         }
         for (int form = 0; form < 3; ++form)
-            for (const uint64_t n : {most, max_particles})
-                if (n > most || more) {
+            for (const uint64_t n : {single, max_particles})
+                if (n > single || more) {
                     const LaunchShape s = resident_shape(h, (double)n, form == 1, form == 2);
                     shapes.push_back({chunks(n, s.chunk), s});
                 }
     }
-    QueueShape most{};
+    most = QueueShape{};
     for (const auto& s : shapes) {
         if (s.first >= (1ull << 29))
             return fail(h, SFQ_E_CAPACITY, "sfq_reserve: too many particles");
@@ -2860,8 +2873,32 @@ sfq_status sfq_reserve(sfq_handle h, uint64_t max_particles, int max_tiles)
         most.entries = std::max(most.entries, q.entries);
         most.deferrable = std::max(most.deferrable, q.deferrable);
     }
+    return SFQ_OK;
+}
+
+extern "C" {
+
+sfq_status sfq_reserve(sfq_handle h, uint64_t max_particles, int max_tiles)
+{
+    if (!h) return fail(h, SFQ_E_STATE, "sfq_reserve: NULL handle");
+    if (max_tiles < 1 || max_tiles > SFQ_MAX_TILES)
+        return fail(h, SFQ_E_ARG, "sfq_reserve: max_tiles in [1, SFQ_MAX_TILES]");
+    std::lock_guard<std::mutex> lock(h->mu);
     HIP_TRY(h, hipSetDevice(h->device));
-    return ensure_queue(h, most, "sfq_reserve");
+    QueueShape most;
+    sfq_status st = reserve_shape(h, max_particles, max_tiles, most);
+    if (st != SFQ_OK) return st;
+    st = ensure_queue(h, most, "sfq_reserve");
+    if (st != SFQ_E_NOMEM || !h->auto_launch) return st;
+    // short of memory: the default set shape, if its queue is smaller
+    h->auto_launch = false;
+    QueueShape set;
+    if (reserve_shape(h, max_particles, max_tiles, set) == SFQ_OK &&
+        queue_bytes(h, set) < queue_bytes(h, most) &&
+        ensure_queue(h, set, "sfq_reserve") == SFQ_OK)
+        return SFQ_OK;
+    h->auto_launch = true;
+    return fail(h, SFQ_E_NOMEM, "sfq_reserve: cannot allocate the emitter queue");
 }
 
 sfq_status sfq_set_queue(sfq_handle h, double expected_fraction, int adaptive)
@@ -2961,7 +2998,7 @@ sfq_status sfq_step(sfq_handle h, const sfq_step_desc* desc, void* stream)
     LaunchShape ls{0, 0};
     const sfq_status v = validate_desc(h, desc, off, ls);
     if (v != SFQ_OK) return v;
-    const int nt = desc->ntiles, chunk = ls.chunk;
+    const int nt = desc->ntiles;
     HIP_TRY(h, hipSetDevice(h->device));
     // A captured step would keep pointers to memory the handle recycles (a staging slot of the
     // descriptors, the emitter queue, which may be reallocated): graphs are made from plans,
@@ -2971,7 +3008,7 @@ sfq_status sfq_step(sfq_handle h, const sfq_step_desc* desc, void* stream)
     if (cap != hipStreamCaptureStatusNone)
         return fail(h, SFQ_E_STATE, "sfq_step: the stream is capturing a graph; capture a plan "
                                     "instead (sfq_plan_create, sfq_plan_capture)");
-    const int nchunks = (int)off[nt];
+    int nchunks = (int)off[nt];
     if (nchunks == 0) {
         // nothing to step; the product counts are still zeroed when asked
         if (desc->zero_product_counts) {
@@ -2988,9 +3025,14 @@ sfq_status sfq_step(sfq_handle h, const sfq_step_desc* desc, void* stream)
         return SFQ_OK;
     }
     adapt_queue(h);
-    const QueueShape qs = queue_shape(nchunks, ls, h->q_frac);
+    QueueShape qs = queue_shape(nchunks, ls, h->q_frac);
     {
-        const sfq_status q = ensure_queue(h, qs, "sfq_step");
+        sfq_status q = ensure_queue(h, qs, "sfq_step");
+        if (q == SFQ_E_NOMEM && smaller_shape(h, desc, off, ls, qs)) {
+            q = ensure_queue(h, qs, "sfq_step");
+            if (q == SFQ_OK) h->auto_launch = false;  // for the steps that follow too
+            nchunks = (int)off[nt];
+        }
         if (q != SFQ_OK) return q;
     }
     // descriptors through a ring of pinned staging buffers and their device copies
@@ -3041,7 +3083,7 @@ sfq_status sfq_step(sfq_handle h, const sfq_step_desc* desc, void* stream)
         HIP_TRY(h, hipEventCreateWithFlags(&h->step_done,
                                            hipEventDisableTiming | hipEventDisableSystemFence));
     StepArgs A;
-    fill_args(h, desc, A, nchunks, chunk);
+    fill_args(h, desc, A, nchunks, ls.chunk);
     A.tiles = (const sfq_tile*)S.dev;
     A.chunk_off = (const uint32_t*)((char*)S.dev + off_pos);
     if (desc->nsets > 0) A.sets = (const sfq_product_set*)((char*)S.dev + set_pos);
@@ -3174,11 +3216,10 @@ sfq_status sfq_plan_create(sfq_handle h, const sfq_step_desc* desc, int zero_pro
     LaunchShape ls{0, 0};
     const sfq_status v = validate_desc(h, desc, off, ls);
     if (v != SFQ_OK) return v;
-    const int nt = desc->ntiles, chunk = ls.chunk;
-    const int nchunks = (int)off[nt];
-    if (nchunks == 0) return fail(h, SFQ_E_ARG, "sfq_plan_create: no particles");
+    const int nt = desc->ntiles;
+    if (off[nt] == 0) return fail(h, SFQ_E_ARG, "sfq_plan_create: no particles");
     HIP_TRY(h, hipSetDevice(h->device));
-    const QueueShape qs = queue_shape(nchunks, ls, h->q_frac);
+    QueueShape qs = queue_shape((int)off[nt], ls, h->q_frac);
     const size_t off_pos = (nt * sizeof(sfq_tile) + 15) & ~(size_t)15;
     const size_t set_pos = (off_pos + (nt + 1) * sizeof(uint32_t) + 15) & ~(size_t)15;
     const size_t step_pos =
@@ -3187,8 +3228,10 @@ sfq_status sfq_plan_create(sfq_handle h, const sfq_step_desc* desc, int zero_pro
     sfq_plan_t* p = new sfq_plan_t();
     p->h = h;
     p->zero_counts = (zero_product_counts || desc->zero_product_counts) ? 1 : 0;
-    if (hipMalloc(&p->d_mem, q_pos + queue_bytes(h, qs)) != hipSuccess) {
+    while (hipMalloc(&p->d_mem, q_pos + queue_bytes(h, qs)) != hipSuccess) {
+        (void)hipGetLastError();
         p->d_mem = nullptr;
+        if (smaller_shape(h, desc, off, ls, qs)) continue;
         plan_release(p);
         return fail(h, SFQ_E_NOMEM, "sfq_plan_create: cannot allocate the plan");
     }
@@ -3207,7 +3250,7 @@ sfq_status sfq_plan_create(sfq_handle h, const sfq_step_desc* desc, int zero_pro
     }
     p->grid = qs.grid;
     p->d_step = (unsigned long long*)((char*)p->d_mem + step_pos);
-    fill_args(h, desc, p->A, nchunks, chunk);
+    fill_args(h, desc, p->A, (int)off[nt], ls.chunk);
     p->A.zero_counts = p->zero_counts;
     p->A.tiles = (const sfq_tile*)p->d_mem;
     p->A.chunk_off = (const uint32_t*)((char*)p->d_mem + off_pos);

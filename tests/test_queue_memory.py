@@ -80,3 +80,33 @@ def test_reserve_holds_what_it_may_need(runtime, form, limits):
         assert all(st == 0 and held == first[1] for st, held, _, _ in rest)
     fixed = runtime(form, (8, 2048), "reserve:" + limits)[0][1]
     assert first[1] <= max(fixed, (min(n, 1 << 23) + (1 << 20)) * ENTRY[form] + books(n, tiles))
+
+
+OUT_OF_MEMORY = 3
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("field", [0, PLANE_WAVE])
+def test_short_memory(runtime, form, field):
+    """Where the picked shape's queue does not fit the device and that of 8 x 2048 does, the step, the
+    plan and the reservation use the latter."""
+    step, plan, reserve = "step:8300000x1", "plan:8300000x1", "reserve:8300000:1"
+    picked, = runtime(form, None, step, field=field)
+    fixed, = runtime(form, (8, 2048), step, field=field)
+    assert fixed[1] < picked[1] and (picked[0], picked[3]) == (0, 4053 if form[1] else 2027)
+    limit = (fixed[2] + picked[2]) // 2
+    st, held, _, grid = runtime(form, None, step, step, limit=limit, field=field)[1]
+    assert (st, grid) == (0, 2048) and held == fixed[1]
+    (st, held, _, grid), small = runtime(form, None, plan, "step:1000x1", limit=limit, field=field)
+    assert (st, grid) == (0, 2048) and (small[0], small[3]) == (0, 4)
+    res = runtime(form, None, reserve, step, "step:65536x1", limit=limit, field=field)
+    assert [r[0] for r in res] == [0, 0, 0] and len({r[1] for r in res}) == 1
+
+
+def test_refused_memory_leaves_nothing_behind(runtime):
+    """A step refused for lack of memory is refused by itself: the handle's next steps, which fit, work
+    and are shaped as before."""
+    for action in ("step:", "plan:", "reserve:"):
+        res = runtime((DEPTH, 0), None, action + ("2000000:1" if action == "reserve:" else "2000000x1"),
+                      "step:1000x1", limit=20_000_000)
+        assert [r[0] for r in res] == [OUT_OF_MEMORY, 0] and res[1][3] == 4
