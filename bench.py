@@ -48,6 +48,13 @@ METRIC = "particle-updates/sec (Compton+BW MC step) FP32 vs FP64; p99 step laten
 HBM_PEAK = 8.0e12  # B/s, MI355X HBM3E
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_bulk_kernel_plane_wave_fp64.md")
 
+PICKED = "picked by the library"
+
+
+def shape_of(tuned):
+    """The launch shape a tuned form runs at, as reported."""
+    return PICKED if tuned.get("picked") else tuned["shape"]
+
 
 def stream_kernel_bytes(n_flags, processed, emitted, converted):
     """Algorithmic bytes of the streaming kernel for one step (optical-depth decisions).  Every
@@ -214,7 +221,7 @@ def run_form(precision, workload, n, steps, warmup, dev, launch=None, push=False
     h.close()
     del tiles, prods, reset
     torch.cuda.empty_cache()
-    return dict(r, n_total=2 * n, n_flags=n_flags, shape=tuned["shape"], queue_bytes=qbytes)
+    return dict(r, n_total=2 * n, n_flags=n_flags, shape=shape_of(tuned), queue_bytes=qbytes)
 
 
 def served_stream_kernel_bytes(n_leptons, n_flags, photons_live):
@@ -272,7 +279,7 @@ def run_served_step(n, steps, warmup, dev, launch=None):
     h.close()
     del tiles, prods, reset, p, k, fperp
     torch.cuda.empty_cache()
-    return dict(r, n_leptons=n, n_flags=n, shape=tuned["shape"])
+    return dict(r, n_leptons=n, n_flags=n, shape=shape_of(tuned))
 
 
 def run_batched(steps, warmup, dev):
@@ -382,7 +389,7 @@ def run_constant_field(dev, n, warmup=2, launch=None):
     cnt = sfq.Counters(dev)
     if launch is not None:
         h.set_launch(*launch)
-    shape = list(launch) if launch is not None else "picked by the library"
+    shape = list(launch) if launch is not None else PICKED
     h.reserve(n, 1)
     for k in range(warmup):
         h.step([tile], seed=seed, step=k, products=pb, counters=cnt, push=True,
@@ -733,7 +740,7 @@ def main():
                           "ms_per_step": batched["device_s"] / K * 1e3,
                           "p50_step_ms": float(np.percentile(batched["step_ms"], 50)),
                           "p99_step_ms": float(np.percentile(batched["step_ms"], 99)),
-                          "launch_shape": batched["tuned"]["shape"],
+                          "launch_shape": shape_of(batched["tuned"]),
                           "autotune_ms": batched["tuned"].get("timings"),
                           "step_roofline": {
                               "frac": survey_step_bytes(pb("processed"), pb("emitted"),

@@ -267,9 +267,11 @@ typedef struct {
  * blocks_per_cu x (number of compute units) blocks of 256 threads, each taking `chunk`
  * consecutive particles of one tile at a time (chunk a multiple of 256 in [256, 2^22]; a tile's
  * first chunk is up to 15 particles shorter, so that the others start at 128-byte lines).
- * Until it is set, every step and plan picks a shape by its number of particles and its form,
- * and sfq_get_launch reports 8 x 2048.  Results do not depend on the launch shape. */
+ * Until it is set, and again after sfq_auto_launch, every step and plan picks a shape by its
+ * particles and its form, and sfq_get_launch reports 8 x 2048.  Results do not depend on the
+ * launch shape. */
 sfq_status sfq_set_launch(sfq_handle h, int blocks_per_cu, int chunk);
+sfq_status sfq_auto_launch(sfq_handle h);
 sfq_status sfq_get_launch(sfq_handle h, int* blocks_per_cu, int* chunk);
 
 

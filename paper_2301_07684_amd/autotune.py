@@ -1,8 +1,8 @@
 """Launch-shape autotuner for the step kernels.
 
 For a given set of tiles it times each candidate launch shape (blocks per compute unit x chunk
-length, see sfq_set_launch) on the real data with a plan, keeps the fastest and caches the
-choice in a JSON file keyed by the device, the precision and a coarse signature of the workload
+length, see sfq_set_launch), and the one the library picks when none is set, on the real data with
+a plan, keeps the fastest and caches the choice in a JSON file keyed by the device, the precision and a coarse signature of the workload
 (total particles and number of tiles rounded to powers of two, species mix).  The particle
 state, the products already in the caller's buffers and the counters are snapshotted before
 tuning and restored afterwards, so a tuned run gives the same results as an untuned one
@@ -89,6 +89,13 @@ def save_cache(cache, path: str = DEFAULT_CACHE):
     os.replace(tmp, path)
 
 
+def _set_shape(handle: sfq.Handle, shape):
+    if shape is None:
+        handle.auto_launch()
+    else:
+        handle.set_launch(*shape)
+
+
 def tune(handle: sfq.Handle, tiles: Sequence[sfq.TileArrays], products: sfq.ProductBuffers,
          counters: sfq.Counters, *, seed: int = 0, step: int = 1,
          candidates: Sequence[Tuple[int, int]] = DEFAULT_CANDIDATES, repeats: int = 4,
@@ -96,13 +103,15 @@ def tune(handle: sfq.Handle, tiles: Sequence[sfq.TileArrays], products: sfq.Prod
          push: bool = False) -> Dict:
     """Sets the fastest launch shape on `handle` and returns {'shape', 'ms', 'timings', ...}.
     Each candidate is timed on the step the caller will run: with `push`, the kernels that push
-    the leptons inside the step."""
+    the leptons inside the step.  With the default candidates the shape that the library picks by
+    size and form is timed too; where it is fastest, 'picked' is true and the handle is left with no
+    shape set ('shape' is what get_launch reports then)."""
     key = signature(handle, tiles, push)
     cache = load_cache(cache_path) if cache_path else {}
     if not force and key in cache:
-        bpc, chunk = cache[key]["shape"]
-        handle.set_launch(bpc, chunk)
-        return dict(cache[key], cached=True, key=key)
+        entry = dict(cache[key], picked=bool(cache[key].get("picked")))
+        _set_shape(handle, None if entry["picked"] else entry["shape"])
+        return dict(entry, cached=True, key=key)
     snap = _snapshot(tiles)
     prod0 = _snapshot_products(products)
     cnt0 = counters.t.clone()
@@ -111,8 +120,11 @@ def tune(handle: sfq.Handle, tiles: Sequence[sfq.TileArrays], products: sfq.Prod
     if was_profiling:
         handle.profile_read_steps()      # the caller's pending timings are not the candidates'
     handle.profile(True)                 # each launch timed by the library's timing-only events
-    for bpc, chunk in candidates:
-        handle.set_launch(bpc, chunk)
+    shapes = {f"{bpc}x{chunk}": (bpc, chunk) for bpc, chunk in candidates}
+    if candidates is DEFAULT_CANDIDATES:
+        shapes["picked"] = None
+    for name, shape in shapes.items():
+        _set_shape(handle, shape)
         plan = handle.plan(tiles, seed=seed, step=step, products=products, counters=counters,
                            push=push)
         plan.launch()
@@ -122,17 +134,17 @@ def tune(handle: sfq.Handle, tiles: Sequence[sfq.TileArrays], products: sfq.Prod
             plan.launch()
         a, b = handle.profile_read_steps()
         ms = sorted((a + b).tolist())    # per launch: streaming kernel to emitter pass end
-        timings[f"{bpc}x{chunk}"] = ms[len(ms) // 2]
+        timings[name] = ms[len(ms) // 2]
         plan.close()
         _restore(tiles, snap)
     handle.profile(was_profiling)
     best = min(timings, key=timings.get)
-    bpc, chunk = (int(v) for v in best.split("x"))
-    handle.set_launch(bpc, chunk)
+    _set_shape(handle, shapes[best])
     _restore_products(products, prod0)
     counters.t.copy_(cnt0)
     torch.cuda.synchronize()
-    entry = {"shape": [bpc, chunk], "ms": timings[best], "timings": timings,
+    entry = {"shape": list(handle.get_launch()), "picked": shapes[best] is None,
+             "ms": timings[best], "timings": timings,
              "when": time.strftime("%Y-%m-%dT%H:%M:%S")}
     if cache_path:
         cache[key] = entry
@@ -190,7 +202,7 @@ def select_form(handle_kwargs: Dict, tiles: Sequence[sfq.TileArrays],
     FP64 or MIXED, with the full or the truncated tables -- whose measured error bound
     (form_errors) is within `max_rel_error`, each also with bw_fast when `allow_bw_fast`, each at
     its own best launch shape, on the caller's tiles, and returns the fastest as {'handle',
-    'precision', 'approx', 'bw_fast', 'name', 'shape', 'ms', 'error_bound', 'timings'}.  The
+    'precision', 'approx', 'bw_fast', 'name', 'shape', 'picked', 'ms', 'error_bound', 'timings'}.  The
     other handles are closed; the particle state, products and counters are restored.
     handle_kwargs are the sfq.Handle arguments other than precision, approx and bw_fast (units,
     dt, decision, blcfa, device); `push` times the steps with the leptons' push."""
@@ -215,7 +227,7 @@ def select_form(handle_kwargs: Dict, tiles: Sequence[sfq.TileArrays],
                 timings[name] = r["ms"]
                 if best is None or r["ms"] < best["ms"]:
                     best = dict(handle=h, precision=prec, approx=approx, bw_fast=bw,
-                                shape=r["shape"], ms=r["ms"], name=name)
+                                shape=r["shape"], picked=r["picked"], ms=r["ms"], name=name)
     finally:
         for h in handles:
             if best is None or h is not best["handle"]:

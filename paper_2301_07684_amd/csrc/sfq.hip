@@ -1847,6 +1847,8 @@ struct ProfEvents {
     int split;  // e[1] recorded between the streaming kernel and the emitter pass
 };
 
+constexpr int DEFAULT_BLOCKS_PER_CU = 8, DEFAULT_CHUNK = 2048;
+
 struct sfq_ctx {
     int device = 0;
     int precision = SFQ_FP64, decision = SFQ_OPTICAL_DEPTH, blcfa = 0, bw_fast = 0;
@@ -1884,8 +1886,8 @@ struct sfq_ctx {
     int last_slot = -1;
     // launch shape of the step kernel (tunable); until it is set, the step picks one by its size
     // and form (auto_shape) and these are only what sfq_get_launch reports
-    int blocks_per_cu = 8;
-    int chunk = 2048;
+    int blocks_per_cu = DEFAULT_BLOCKS_PER_CU;
+    int chunk = DEFAULT_CHUNK;
     bool auto_launch = true;
     // kernel timing (sfq_profile_*): events around the two step kernels of each timed step
     int prof = 0;
@@ -2284,6 +2286,16 @@ sfq_status sfq_set_launch(sfq_handle h, int blocks_per_cu, int chunk)
     h->blocks_per_cu = blocks_per_cu;
     h->chunk = chunk;
     h->auto_launch = false;
+    return SFQ_OK;
+}
+
+sfq_status sfq_auto_launch(sfq_handle h)
+{
+    if (!h) return fail(h, SFQ_E_STATE, "sfq_auto_launch: NULL handle");
+    std::lock_guard<std::mutex> lock(h->mu);
+    h->blocks_per_cu = DEFAULT_BLOCKS_PER_CU;
+    h->chunk = DEFAULT_CHUNK;
+    h->auto_launch = true;
     return SFQ_OK;
 }
 

@@ -33,7 +33,7 @@ STATUS = {0: "SFQ_OK", 1: "SFQ_E_ARG", 2: "SFQ_E_STATE", 3: "SFQ_E_NOMEM", 4: "S
 # every symbol declared in include/sfq.h
 EXPORTS = ("sfq_create", "sfq_destroy", "sfq_last_error", "sfq_units", "sfq_chi", "sfq_rates",
            "sfq_sample_photon", "sfq_sample_pair", "sfq_philox", "sfq_init_optical_depth",
-           "sfq_step", "sfq_step_noalloc", "sfq_set_launch", "sfq_get_launch", "sfq_plan_create",
+           "sfq_step", "sfq_step_noalloc", "sfq_set_launch", "sfq_auto_launch", "sfq_get_launch", "sfq_plan_create",
            "sfq_plan_destroy",
            "sfq_plan_launch", "sfq_plan_set_step", "sfq_plan_capture", "sfq_plan_replay",
            "sfq_reserve", "sfq_set_queue", "sfq_queue_bytes", "sfq_profile_enable",
@@ -134,6 +134,8 @@ def load(path: str = LIB_PATH):
     L.sfq_step_noalloc.argtypes = [vp, C.POINTER(StepDesc), vp]
     L.sfq_set_launch.restype = st
     L.sfq_set_launch.argtypes = [vp, C.c_int, C.c_int]
+    L.sfq_auto_launch.restype = st
+    L.sfq_auto_launch.argtypes = [vp]
     L.sfq_get_launch.restype = st
     L.sfq_get_launch.argtypes = [vp, C.POINTER(C.c_int), C.POINTER(C.c_int)]
     L.sfq_plan_create.restype = st
@@ -259,6 +261,10 @@ class Handle:
 
     def set_launch(self, blocks_per_cu: int, chunk: int):
         self._check(self._L.sfq_set_launch(self._h, blocks_per_cu, chunk))
+
+    def auto_launch(self):
+        """Unset the launch shape: steps and plans pick one by size and form, as on a new handle."""
+        self._check(self._L.sfq_auto_launch(self._h))
 
     def get_launch(self):
         a, b = C.c_int(), C.c_int()

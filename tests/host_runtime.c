@@ -7,6 +7,7 @@
  *   reserve:N:T       sfq_reserve
  *   step:NxK,NxK,...  sfq_step of K tiles of N electrons, ...; noalloc: and plan: the same
  *   limit:B           another limit
+ *   auto:             sfq_auto_launch
  * Each action prints its status, the handle's queue bytes, the most device memory in use beyond
  * sfq_create's so far in the action, and the blocks of the last streaming kernel. */
 #include <hip/hip_runtime_api.h>
@@ -168,6 +169,8 @@ int main(int argc, char** argv)
         if (!strncmp(argv[k], "limit", 5)) {
             limit = strtoull(arg, NULL, 10);
             continue;
+        } else if (!strncmp(argv[k], "auto", 4)) {
+            st = sfq_auto_launch(h);
         } else if (!strncmp(argv[k], "reserve", 7)) {
             unsigned long long n;
             int t;

@@ -110,3 +110,10 @@ def test_refused_memory_leaves_nothing_behind(runtime):
         res = runtime((DEPTH, 0), None, action + ("2000000:1" if action == "reserve:" else "2000000x1"),
                       "step:1000x1", limit=20_000_000)
         assert [r[0] for r in res] == [OUT_OF_MEMORY, 0] and res[1][3] == 4
+
+
+def test_unset_shape(runtime):
+    """A handle whose shape was set picks again after sfq_auto_launch."""
+    res = runtime((DEPTH, 0), (8, 2048), "step:65536x1", "auto:", "step:65536x1", "step:2000000x1")
+    assert [r[0] for r in res] == [0, 0, 0, 0]
+    assert [r[3] for r in res] == [33, 33, 257, 489]
