@@ -292,9 +292,10 @@ sfq_status sfq_step(sfq_handle h, const sfq_step_desc* desc, void* stream);
  * deferred-share list) lives in a static device array of 256 MiB that the library holds on
  * each device it runs on until the process ends; sfq_create sets it up, with a pinned buffer
  * per handle for the descriptors.  The queue takes what the array leaves: shares that do not
- * fit are stepped by the deferred-share kernel, so results never depend on it (the call uses
- * the handle's launch shape, with the chunk halved while one share per slice would take more
- * than half of the queue's room).  Steps with more chunks than the array can list (about
+ * fit are stepped by the deferred-share kernel, so results never depend on it.  Where no launch
+ * shape is set and the array holds the whole queue of the shape picked for the step, the call uses
+ * that; otherwise the shape that is set (or 8 x 2048), with the chunk halved while one share per
+ * slice would take more than half of the queue's room.  Steps with more chunks than the array can list (about
  * sixteen million), or descriptors beyond 2 MiB, return SFQ_E_CAPACITY and enqueue nothing; a
  * capturing stream returns SFQ_E_STATE.  All calls on one
  * device share the array, and it keeps the last call's contents: calls that overlap on one
@@ -312,9 +313,9 @@ typedef struct sfq_plan_t* sfq_plan;
 
 /* Creates a plan for the tiles and buffers of `desc` (pointers are kept, the tile array is
  * copied; desc->step is the first step index).  zero_product_counts = 1 (or
- * desc->zero_product_counts = 1) zeroes the product counts at the start of every step (with a
- * kernel).  The handle's launch shape
- * (sfq_set_launch) at creation time is used.  The plan must be destroyed before the handle. */
+ * desc->zero_product_counts = 1) zeroes the product counts at the start of every step (in its
+ * kernels).  The launch shape that is set (sfq_set_launch) or picked at creation time is used.
+ * The plan must be destroyed before the handle. */
 sfq_status sfq_plan_create(sfq_handle h, const sfq_step_desc* desc, int zero_product_counts,
                            sfq_plan* out);
 void sfq_plan_destroy(sfq_plan p);

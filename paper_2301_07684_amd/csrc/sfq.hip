@@ -352,8 +352,11 @@ constexpr int bulk_waves(bool mixed, bool blcfa, bool push, bool wave)
 #ifndef SFQ_EMIT_WAVES
 #define SFQ_EMIT_WAVES 3
 #endif
-// Emitters dense: above this fraction of the step's particles the emitter kernel writes the
-// products with non-temporal stores (measured faster at 10-13 % emitters and slower at 2 %).
+// Emitters dense: above this fraction of the step's particle slots the emitter kernel writes the
+// products with non-temporal stores (measured faster at 10-13 % emitters and slower at 2 %, one
+// density throughout).  One choice for the whole step: where tiles differ it makes no difference (2
+// million at 17 % beside 14 million at 0.3 % 47 us with either store, 4 at 13 % beside 12 at 0.5 %
+// 67, every second or fourth of 64 tiles at 20 % 41 and 30, 8 million of which 60 % are dead 61).
 constexpr float DENSE_EMITTER_FRACTION = 0.06f;
 
 // read as the alive flag of tiles that have no alive array
@@ -507,7 +510,7 @@ struct EmitCounts {
 };
 
 // One product into slot k of a product buffer; nt: non-temporal stores (the emitter kernel uses
-// them where emitters are dense, see emit_item)
+// them where emitters are dense, see DENSE_EMITTER_FRACTION)
 __device__ __forceinline__ void store_product(const sfq_products& P, unsigned long long k,
                                               double px, double py, double pz, double tau,
                                               uint64_t uid, uint64_t parent, bool nt)
@@ -1397,7 +1400,9 @@ __device__ __forceinline__ EmitRows emit_rows(int grid)
 // w-th quarter, 64 rows at a time: whole lines read, all reads in flight together, neighbouring
 // words of shared memory.  (A few rows next to each other per thread: 8 us for 2900 rows, for the
 // bank conflicts, or, read directly, for a line per lane and read.)
-// The step's emitters number fewer than 2^32: a queue entry takes 48 B.
+// The step's emitters number fewer than 2^32: each has a momentum (24 B) and an entry of at least 56 B
+// with its id queued, or a depth and an entry of 48 B, and 2^32 times 80 B are 344 GB, more than the
+// device holds.
 __device__ __forceinline__ void emit_prefix(const StepArgs& A, EmitShared& sh, const EmitRows& R,
                                             uint32_t& total_l, uint32_t& total_p)
 {
@@ -1885,7 +1890,7 @@ struct sfq_ctx {
     std::vector<char> last_desc, desc_bytes;
     int last_slot = -1;
     // launch shape of the step kernel (tunable); until it is set, the step picks one by its size
-    // and form (auto_shape) and these are only what sfq_get_launch reports
+    // and form (launch_shape) and these are only what sfq_get_launch reports
     int blocks_per_cu = DEFAULT_BLOCKS_PER_CU;
     int chunk = DEFAULT_CHUNK;
     bool auto_launch = true;
@@ -2489,8 +2494,7 @@ static sfq_status validate_desc(sfq_ctx* h, const sfq_step_desc* desc, std::vect
 // The most chunks one streaming block may take: its even share and a sixteenth more (at least
 // one), so that fast blocks take over from slow ones at the end of the step (none more below 4
 // chunks per block, where a step is short and a larger worst case would only defer shares).
-// The queue's worst case is sized for it.  A small surplus keeps the emitter blocks' work,
-// which follows the streaming blocks' slices, nearly even.
+// The queue's worst case is sized for it, so the surplus is kept small.
 static int max_chunks_per_block(int nchunks, int grid)
 {
     const int even = (nchunks + grid - 1) / grid;

@@ -39,9 +39,11 @@ from . import inputs, sfq
 LEPTON_BYTES = 8 * 3 * 3 + 8 + 1 + 8 + 8  # p, F_perp, dF; uid; just_created; wave a, phi
 PHOTON_BYTES = 8 * 3 + 8 + 1 + 8 + 8       # p; uid; alive; wave a, phi
 PRODUCT_BYTES = 6 * 8                      # p, tau, uid, parent
-# launch shape of the lanes' steps (blocks per compute unit, particles per chunk): the best of
-# 8 x 2048, 3 x 4096, 4 x 2048 and 3 x 2048 on the served workload (batches of about 24M
-# particles in beyond-LCFA kernels of 3 waves per SIMD), by a few percent
+# launch shape of the lanes' steps (blocks per compute unit, particles per chunk), also the one the
+# library picks for batches above 8.4 million particles: a batch of 24 million (MIXED, six
+# simulations) takes 723 us, 733 at 8 x 2048, 730 at 3 x 4096, 754 at 3 x 2048, 703 at 4 x 4096, whose
+# queue is half as large again (566 MB a lane against 397, charged to the budget); one of 6 million
+# 210, 200 at the shape picked there (434 MB against 208)
 LANE_LAUNCH = (4, 2048)
 # expected emitter fraction the lanes' emitter queues are sized for (fixed, so that their memory
 # is known when admitting; a batch with more emitters is still stepped exactly, more slowly)
