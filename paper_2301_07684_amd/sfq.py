@@ -181,15 +181,10 @@ def _three(v):
     return v if type(v) is tuple and len(v) == 3 else _vec3(*v)
 
 
-def _pack_tile(tile, buffer, offset):
-    """The tile's record at `offset` of `buffer`, holding what the fields of Tile take: values that the
-    packed form refuses (whole numbers wider than a field, which are cut to it) go through those."""
-    record = tile._record()
-    try:
-        _TILE.pack_into(buffer, offset, *record)
-    except struct.error:
-        t = Tile(*record[:28], _vec3(*record[28:31]), _vec3(*record[31:34]), record[34])
-        C.memmove(C.addressof(buffer) + offset, C.addressof(t), _TILE.size)
+# Whole numbers wider than their field, which the packed records refuse, are cut to it by ctypes.
+def _pack_tile_fields(buffer, offset, record):
+    t = Tile(*record[:28], _vec3(*record[28:31]), _vec3(*record[31:34]), record[34])
+    C.memmove(C.addressof(buffer) + offset, C.addressof(t), _TILE.size)
 
 
 # torch's own handle of a device's current stream, without the Stream object that
@@ -378,7 +373,11 @@ class Handle:
             raise ValueError("1 <= len(tiles) <= MAX_TILES")
         arr = (Tile * nt)()
         for k, t in enumerate(tiles):
-            _pack_tile(t, arr, k * _TILE.size)
+            record = t._record()
+            try:
+                _TILE.pack_into(arr, k * _TILE.size, *record)
+            except struct.error:
+                _pack_tile_fields(arr, k * _TILE.size, record)
         if product_sets:
             nsets = len(product_sets)
             sets = (ProductSetC * nsets)()
@@ -397,10 +396,14 @@ class Handle:
                  *products.positrons._record(), _address(products.counts))
                 if products else (*_NO_PRODUCTS, *_NO_PRODUCTS, *_NO_PRODUCTS, 0))
         desc = StepDesc()
-        _STEP.pack_into(desc, 0, 0, 0, nt, nsets, C.addressof(arr), *made,
-                        _address(counters.t), C.addressof(sets) if sets is not None else 0,
-                        int(bool(push)), int(bool(zero_product_counts)))
-        desc.seed, desc.step = seed, step  # any integer type, modulo 2^64
+        rest = (nt, nsets, C.addressof(arr), *made, _address(counters.t),
+                C.addressof(sets) if sets is not None else 0, int(bool(push)),
+                int(bool(zero_product_counts)))
+        try:
+            _STEP.pack_into(desc, 0, seed, step, *rest)
+        except struct.error:
+            _STEP.pack_into(desc, 0, 0, 0, *rest)
+            desc.seed, desc.step = seed, step
         return desc, (arr, sets)
 
     def step(self, tiles: Sequence["TileArrays"], *, seed: int, step: int,
@@ -549,7 +552,11 @@ class TileArrays:
 
     def to_c(self) -> Tile:
         t = Tile()
-        _pack_tile(self, t, 0)
+        record = self._record()
+        try:
+            _TILE.pack_into(t, 0, *record)
+        except struct.error:
+            _pack_tile_fields(t, 0, record)
         return t
 
 
