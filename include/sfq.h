@@ -346,7 +346,8 @@ sfq_status sfq_plan_replay(sfq_plan p, void* stream);
  * Where no launch shape is set, steps of up to about 8.4 million particles give every block one
  * chunk, and the queue then has an entry for every slot of the chunks, whatever the fraction: at
  * most one per particle and 2^20 more (48 to 72 bytes each; steps whose tiles would need more,
- * because they end far inside their chunks, run on fewer blocks, with a queue by the fraction).
+ * because they end far inside their chunks, run as larger ones do).  Larger steps run on fewer
+ * blocks than 8 x 2048 has, whose slices hold more: together at least what those of 8 x 2048 do.
  * A step, plan or reservation whose queue the device's memory does not hold takes the shape
  * 8 x 2048 instead if its queue is smaller (a step or reservation for the handle's later steps too).
  *

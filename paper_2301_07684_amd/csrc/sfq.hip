@@ -2322,6 +2322,8 @@ sfq_status sfq_get_launch(sfq_handle h, int* blocks_per_cu, int* chunk)
 struct LaunchShape {
     int max_blocks;
     int chunk;
+    uint64_t default_chunks = 0;  // if not 0: the chunks the step has at the default set shape, whose
+                                  // queue this shape's is not to be smaller than
 };
 
 static LaunchShape set_shape(const sfq_ctx* h)
@@ -2380,9 +2382,9 @@ static LaunchShape resident_shape(const sfq_ctx* h, double n, bool wave, bool un
 // particles: beyond this many entries (50 to 75 MB) more than one per particle, the step runs on
 // resident blocks, whose queue follows the expected emitters.  Those are no slower there, since
 // thousands of blocks with little each also lengthen the emitter pass: 4096 tiles of 1000 particles
-// 131 us with a chunk each (806 MB), 126 resident (107 MB); 4096 of 500 96 and 92; one of 4 million
-// and 4095 of 100 151 (998 MB) and 152 (132 MB); 1000 tiles of 100 to 50,000 212 and 197 (beyond LCFA
-// 536, 688 MB, and 551, 271 MB).
+// 131 us with a chunk each (806 MB), 126 resident (252 MB); 4096 of 500 96 and 92; one of 4 million
+// and 4095 of 100 151 (998 MB) and 152 (277 MB); 1000 tiles of 100 to 50,000 212 and 197 (beyond LCFA
+// 536, 688 MB, and 548, 419 MB).
 constexpr uint64_t QUEUE_SLACK = 1ull << 20;
 
 static LaunchShape launch_shape(const sfq_ctx* h, const sfq_step_desc* desc)
@@ -2401,7 +2403,10 @@ static LaunchShape launch_shape(const sfq_ctx* h, const sfq_step_desc* desc)
         for (int t = 0; t < desc->ntiles; ++t) nch += tile_chunks(desc->tiles[t], one.chunk);
         if (nch * (uint64_t)one.chunk <= (uint64_t)n + QUEUE_SLACK) return one;
     }
-    return resident_shape(h, n, wave, uniform);
+    LaunchShape res = resident_shape(h, n, wave, uniform);
+    for (int t = 0; t < desc->ntiles; ++t)
+        res.default_chunks += tile_chunks(desc->tiles[t], DEFAULT_CHUNK);
+    return res;
 }
 
 // Checks the descriptor and fills the tiles' chunk offsets for the launch shape `ls`, or, if that
@@ -2514,7 +2519,11 @@ struct QueueShape {
 // The queue of a step of nchunks chunks.  A wave's slice holds one share of a chunk (what one
 // chunk can add to it) plus the fraction `frac` of every particle of the wave's shares (the
 // expected emitters with headroom), at most all of them: then no share is ever deferred.
-static QueueShape queue_shape(int nchunks, const LaunchShape& ls, double frac)
+// The share is most of that headroom where blocks are many and take few chunks, and little where
+// picked resident blocks take many: those slices get what the default shape's queue has room for
+// besides (first step of 16.8 million of which 20 % emit: 5.1 million deferred and 1650 us without, none
+// and 662 with; 2^25 of which 15 % emit: 3.3 million and 1901, none and 1259).
+static QueueShape queue_shape(const sfq_ctx* h, int nchunks, const LaunchShape& ls, double frac)
 {
     const int chunk = ls.chunk;
     QueueShape q;
@@ -2526,6 +2535,12 @@ static QueueShape queue_shape(int nchunks, const LaunchShape& ls, double frac)
     const uint64_t worst = chunks_per_block * share;
     const double want = (double)share + std::ceil(std::max(0.0, frac) * (double)worst);
     q.cap_per_wave = std::max<uint64_t>(1, std::min<uint64_t>(worst, (uint64_t)want));
+    if (ls.default_chunks) {
+        const LaunchShape set{DEFAULT_BLOCKS_PER_CU * h->num_cus, DEFAULT_CHUNK};
+        const int nch = (int)std::min<uint64_t>(ls.default_chunks, (1ull << 29) - 1);
+        const uint64_t least = queue_shape(h, nch, set, frac).entries;
+        q.cap_per_wave = std::min(worst, std::max(q.cap_per_wave, least / q.slices));
+    }
     q.may_defer = q.cap_per_wave < worst ? 1 : 0;
     q.entries = q.slices * q.cap_per_wave;
     q.deferrable = (uint64_t)STEP_WAVES * (uint64_t)std::max(nchunks, 1);
@@ -2842,7 +2857,7 @@ static bool smaller_shape(sfq_ctx* h, const sfq_step_desc* desc, std::vector<uin
     LaunchShape set = set_shape(h);
     std::vector<uint32_t> set_off;
     if (validate_desc(h, desc, set_off, set) != SFQ_OK) return false;
-    const QueueShape q = queue_shape((int)set_off[desc->ntiles], set, h->q_frac);
+    const QueueShape q = queue_shape(h, (int)set_off[desc->ntiles], set, h->q_frac);
     if (queue_bytes(h, q) >= queue_bytes(h, qs)) return false;
     off.swap(set_off);
     ls = set;
@@ -2875,7 +2890,8 @@ static sfq_status reserve_shape(sfq_ctx* h, uint64_t max_particles, int max_tile
         for (int form = 0; form < 3; ++form)
             for (const uint64_t n : {single, max_particles})
                 if (n > single || more) {
-                    const LaunchShape s = resident_shape(h, (double)n, form == 1, form == 2);
+                    LaunchShape s = resident_shape(h, (double)n, form == 1, form == 2);
+                    s.default_chunks = chunks(n, DEFAULT_CHUNK);
                     shapes.push_back({chunks(n, s.chunk), s});
                 }
     }
@@ -2883,7 +2899,7 @@ static sfq_status reserve_shape(sfq_ctx* h, uint64_t max_particles, int max_tile
     for (const auto& s : shapes) {
         if (s.first >= (1ull << 29))
             return fail(h, SFQ_E_CAPACITY, "sfq_reserve: too many particles");
-        const QueueShape q = queue_shape((int)s.first, s.second, h->q_frac);
+        const QueueShape q = queue_shape(h, (int)s.first, s.second, h->q_frac);
         most.grid = std::max(most.grid, q.grid);
         most.slices = std::max(most.slices, q.slices);
         most.entries = std::max(most.entries, q.entries);
@@ -3041,7 +3057,7 @@ sfq_status sfq_step(sfq_handle h, const sfq_step_desc* desc, void* stream)
         return SFQ_OK;
     }
     adapt_queue(h);
-    QueueShape qs = queue_shape(nchunks, ls, h->q_frac);
+    QueueShape qs = queue_shape(h, nchunks, ls, h->q_frac);
     {
         sfq_status q = ensure_queue(h, qs, "sfq_step");
         if (q == SFQ_E_NOMEM && smaller_shape(h, desc, off, ls, qs)) {
@@ -3139,7 +3155,7 @@ sfq_status sfq_step_noalloc(sfq_handle h, const sfq_step_desc* desc, void* strea
     sfq_status v = validate_desc(h, desc, off, ls);
     if (v != SFQ_OK) return v;
     const int nt = desc->ntiles;
-    if (!h->auto_launch || queue_bytes(h, queue_shape((int)off[nt], ls, 1.0)) > room) {
+    if (!h->auto_launch || queue_bytes(h, queue_shape(h, (int)off[nt], ls, 1.0)) > room) {
         ls = set_shape(h);
         const uint64_t slices = (uint64_t)ls.max_blocks * STEP_WAVES;
         while (ls.chunk > STEP_BLOCK &&
@@ -3180,7 +3196,7 @@ sfq_status sfq_step_noalloc(sfq_handle h, const sfq_step_desc* desc, void* strea
                                            std::to_string(STAGING_BYTES) + " bytes for them");
     // the queue: the rest of the scratch, its slices as large as it allows (at most the worst
     // case); shares that do not fit are stepped by the deferred-share kernel
-    QueueShape qs = queue_shape(nchunks, ls, 1.0);
+    QueueShape qs = queue_shape(h, nchunks, ls, 1.0);
     const uint64_t worst = qs.cap_per_wave;
     QueueShape probe = qs;
     probe.entries = 0;
@@ -3235,7 +3251,7 @@ sfq_status sfq_plan_create(sfq_handle h, const sfq_step_desc* desc, int zero_pro
     const int nt = desc->ntiles;
     if (off[nt] == 0) return fail(h, SFQ_E_ARG, "sfq_plan_create: no particles");
     HIP_TRY(h, hipSetDevice(h->device));
-    QueueShape qs = queue_shape((int)off[nt], ls, h->q_frac);
+    QueueShape qs = queue_shape(h, (int)off[nt], ls, h->q_frac);
     const size_t off_pos = (nt * sizeof(sfq_tile) + 15) & ~(size_t)15;
     const size_t set_pos = (off_pos + (nt + 1) * sizeof(uint32_t) + 15) & ~(size_t)15;
     const size_t step_pos =

@@ -117,3 +117,19 @@ def test_unset_shape(runtime):
     res = runtime((DEPTH, 0), (8, 2048), "step:65536x1", "auto:", "step:65536x1", "step:2000000x1")
     assert [r[0] for r in res] == [0, 0, 0, 0]
     assert [r[3] for r in res] == [33, 33, 257, 489]
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("layout", ["9000000x1", "16777216x2", "200000000x1", "1000x4096",
+                                    "50000x100,17x3000", "9000000x1,5x4000"])
+def test_resident_blocks_hold_as_many_emitters(runtime, form, layout):
+    """The resident blocks of a picked shape are fewer than those of 8 x 2048; their queue holds as
+    many entries, so that no more shares are deferred."""
+    for field in (0, 1, PLANE_WAVE):
+        (st, held, _, grid), = runtime(form, None, "step:" + layout, field=field)
+        (_, fixed, _, blocks), = runtime(form, (8, 2048), "step:" + layout, field=field)
+        assert st == 0 and grid < blocks
+        # beside the entries: 52 bytes a block and 16 a chunk, some alignment, and what does not divide
+        # by the slices
+        chunks = particles(layout) // 2048 + 4096
+        assert held >= fixed - 64 * blocks - 16 * chunks - 4 * grid * ENTRY[form]
