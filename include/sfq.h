@@ -353,9 +353,9 @@ sfq_status sfq_plan_replay(sfq_plan p, void* stream);
  *
  * Pre-sizes the queue for sfq_step calls of up to `max_particles` particles in up to
  * `max_tiles` tiles with the launch shape that is set, or any that such calls pick where none is,
- * and the current queue fraction, so that such calls allocate nothing.  A larger step, one after a change of launch shape, or one after the queue
- * fraction grew still grows the queue, which waits for the device.  SFQ_E_NOMEM if the
- * allocation fails. */
+ * and the current queue fraction, so that such calls allocate nothing.  A larger step, one after a
+ * change of launch shape, or one after the queue fraction grew still grows the queue, which waits
+ * for the device.  SFQ_E_NOMEM if the allocation fails. */
 sfq_status sfq_reserve(sfq_handle h, uint64_t max_particles, int max_tiles);
 
 /* Sizing of the emitter queue: `expected_fraction` in [0, 1] is the fraction of a step's
