@@ -295,10 +295,9 @@ sfq_status sfq_step(sfq_handle h, const sfq_step_desc* desc, void* stream);
  * fit are stepped by the deferred-share kernel, so results never depend on it.  Where no launch
  * shape is set and the array holds the whole queue of the shape picked for the step, the call uses
  * that; otherwise the shape that is set (or 8 x 2048), with the chunk halved while one share per
- * slice would take more than half of the queue's room.  Steps with more chunks than the array can list (about
- * sixteen million), or descriptors beyond 2 MiB, return SFQ_E_CAPACITY and enqueue nothing; a
- * capturing stream returns SFQ_E_STATE.  All calls on one
- * device share the array, and it keeps the last call's contents: calls that overlap on one
+ * slice would take more than half of the queue's room.  Steps with more chunks than the array can
+ * list (about sixteen million), or descriptors beyond 2 MiB, return SFQ_E_CAPACITY and enqueue
+ * nothing; a capturing stream returns SFQ_E_STATE.  All calls on one device share the array, and it keeps the last call's contents: calls that overlap on one
  * device (other streams, other handles, other threads) race and must be ordered by the caller;
  * calls on one stream are ordered by it.  Timing events (sfq_profile_*) are not recorded. */
 sfq_status sfq_step_noalloc(sfq_handle h, const sfq_step_desc* desc, void* stream);

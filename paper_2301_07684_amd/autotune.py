@@ -2,8 +2,8 @@
 
 For a given set of tiles it times each candidate launch shape (blocks per compute unit x chunk
 length, see sfq_set_launch), and the one the library picks when none is set, on the real data with
-a plan, keeps the fastest and caches the choice in a JSON file keyed by the device, the precision and a coarse signature of the workload
-(total particles and number of tiles rounded to powers of two, species mix).  The particle
+a plan, keeps the fastest and caches the choice in a JSON file keyed by the device, the precision
+and a coarse signature of the workload (total particles and number of tiles rounded to powers of two, species mix).  The particle
 state, the products already in the caller's buffers and the counters are snapshotted before
 tuning and restored afterwards, so a tuned run gives the same results as an untuned one
 (results never depend on the launch shape).

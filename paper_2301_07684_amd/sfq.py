@@ -33,9 +33,8 @@ STATUS = {0: "SFQ_OK", 1: "SFQ_E_ARG", 2: "SFQ_E_STATE", 3: "SFQ_E_NOMEM", 4: "S
 # every symbol declared in include/sfq.h
 EXPORTS = ("sfq_create", "sfq_destroy", "sfq_last_error", "sfq_units", "sfq_chi", "sfq_rates",
            "sfq_sample_photon", "sfq_sample_pair", "sfq_philox", "sfq_init_optical_depth",
-           "sfq_step", "sfq_step_noalloc", "sfq_set_launch", "sfq_auto_launch", "sfq_get_launch", "sfq_plan_create",
-           "sfq_plan_destroy",
-           "sfq_plan_launch", "sfq_plan_set_step", "sfq_plan_capture", "sfq_plan_replay",
+           "sfq_step", "sfq_step_noalloc", "sfq_set_launch", "sfq_auto_launch", "sfq_get_launch",
+           "sfq_plan_create", "sfq_plan_destroy", "sfq_plan_launch", "sfq_plan_set_step", "sfq_plan_capture", "sfq_plan_replay",
            "sfq_reserve", "sfq_set_queue", "sfq_queue_bytes", "sfq_profile_enable",
            "sfq_profile_read", "sfq_profile_read_steps")
 
